@@ -305,6 +305,29 @@ hipError_t launch_iota(int32_t count, int32_t* out, hipStream_t st);
 hipError_t launch_check_finite(int64_t n, const double* x, const double* v, const double* a,
                                const double* j, int32_t* flag, hipStream_t st);
 
+// Full FP64 sweeps by pairs (pairs.hip): the shape of one, fixed on the host.
+constexpr int kPairMaxLevels = 60;
+struct PairShape {
+    int32_t k, w;         // particles per lane, waves per workgroup
+    int32_t bi;           // particles of an i-block, 64 k w (a j tile holds 64 w)
+    int32_t nch;          // i-side partial-sum slots: chunks of the longest row
+    int32_t items;        // work items of one system
+    int32_t reserved;
+    int16_t lev[kPairMaxLevels + 2];   // chunk c of a row: j tiles [lev[c], lev[c+1])
+};
+
+// The shape for a full sweep of n particles in n_clusters systems of at most
+// n_cmax; false where the one-sided sweep is the better or the only one.
+bool pair_shape(int64_t n, int n_clusters, int64_t n_cmax, int n_cu, bool pot_only,
+                PairShape* sh);
+// Doubles of partial sums that the shape needs.
+int64_t pair_partial_doubles(const PairShape& sh, int64_t n, int64_t n_cmax, bool pot_only);
+// The pair sweep of a (every particle active, FP64, a.partial of that many
+// doubles): for ensembles a plan kernel, then the sweep and the reduction.
+// queue: one device word of scratch.  marks as in launch_force.
+hipError_t launch_pairs(const SweepArgs& a, const PairShape& sh, uint32_t* queue, int n_cu,
+                        bool pot_only, hipStream_t st, const hipEvent_t* marks = nullptr);
+
 int sweep_occupancy(int precision, int variant, bool pot_only);
 
 hipError_t launch_energy_reduce(int64_t n, int n_clusters,

@@ -80,6 +80,7 @@ struct hermite_ctx {
     // per-cluster tables and partial sums, and the flagging reduce's ticket
     Buf ref_pos, ref_idx, ref_p, ref_tmp, ref_ucnt, ref_ccnt, rplan, ract_start, ract_cnt,
         rchunks, ritem_off;
+    Buf pair;   // full FP64 sweeps by pairs: the queue word, then the partial sums
     Buf sel_min, sel_cnt;
     Buf step_idx, step_na, step_T, step_out, step_acl, phi, counters, ticket, flag;
     // step-size order of a run (hermite_run)
@@ -431,14 +432,66 @@ int prepare_refine(hermite_ctx* c, const SweepArgs& a, SweepArgs* ra)
     return HERMITE_OK;
 }
 
-int run_force(hermite_ctx* c, const SweepArgs& a, int precision, const hermite_tuning& tu,
-              bool pot_only, hipStream_t st)
+// True when the sweep can go by pairs: the host knows that every particle is
+// active (no list, no device count) and every system is swept in FP64.
+bool pairs_fit(const SweepArgs& a, int precision, int n_cu, bool pot_only, PairShape* sh)
 {
+    const bool fp64 = precision == HERMITE_FP64 ||
+                      ((precision == HERMITE_MIXED || precision == HERMITE_MIXED_2F) && !a.refine);
+    return fp64 && !a.idx && !a.n_act_dev && a.n_act_max == a.n && !a.pred_x &&
+           pair_shape(a.n, a.n_clusters, a.n_cmax, n_cu, pot_only, sh);
+}
+
+// The context's partial sums of a pair sweep, or false where they cannot be
+// had (more than kPairMaxBytes, no memory, or a stream under capture that
+// would need an allocation): the one-sided sweep, whose scratch exists, then
+// does the work.  No captured step refers to this buffer.
+constexpr int64_t kPairMaxBytes = (int64_t)4 << 30;
+
+constexpr size_t kPairHead = 256;
+
+bool pair_scratch(hermite_ctx* c, int64_t doubles, hipStream_t st)
+{
+    const size_t need = kPairHead + sizeof(double) * (size_t)doubles;
+    if ((int64_t)need > kPairMaxBytes) return false;
+    if (c->pair.bytes >= need) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (cap != hipStreamCaptureStatusNone) return false;
+    if (c->pair.p) {
+        if (hipDeviceSynchronize() != hipSuccess) return false;
+        (void)hipFree(c->pair.p);
+        c->pair = Buf();
+    }
+    void* p = nullptr;
+    if (hipMalloc(&p, need) != hipSuccess || !p) {
+        (void)hipGetLastError();
+        return false;
+    }
+    c->pair.p = p;
+    c->pair.bytes = need;
+    return true;
+}
+
+int run_force(hermite_ctx* c, const SweepArgs& a, int precision, const hermite_tuning& tu,
+              bool pot_only, hipStream_t st, const hipEvent_t* marks = nullptr)
+{
+    PairShape sh;
+    if (pairs_fit(a, precision, c->n_cu, pot_only, &sh) &&
+        pair_scratch(c, pair_partial_doubles(sh, a.n, a.n_cmax, pot_only), st)) {
+        SweepArgs b = a;
+        b.partial = (double*)((char*)c->pair.p + kPairHead);
+        HIP_OK(launch_pairs(b, sh, (uint32_t*)c->pair.p, c->n_cu, pot_only, st, marks));
+        return HERMITE_OK;
+    }
     const int grid = std::max(1, c->n_cu * tu.wg_per_cu);
     SweepArgs ra;
     if (a.refine && !pot_only) CHECK(prepare_refine(c, a, &ra));
     HIP_OK(launch_force(a, (a.refine && !pot_only) ? &ra : nullptr, precision, tu.variant, grid,
-                        pot_only, st));
+                        pot_only, st, marks));
     return HERMITE_OK;
 }
 
@@ -823,6 +876,7 @@ int hermite_destroy(hermite_ctx* c)
                    &c->partial, &c->ref_pos, &c->ref_idx, &c->ref_p, &c->ref_tmp,
                    &c->ref_ucnt, &c->ref_ccnt,
                    &c->rplan, &c->ract_start, &c->ract_cnt, &c->rchunks, &c->ritem_off,
+                   &c->pair,
                    &c->sel_min, &c->sel_cnt, &c->step_idx, &c->step_na,
                    &c->step_T, &c->step_out, &c->step_acl, &c->phi, &c->counters,
                    &c->ticket, &c->flag, &c->lvl_perm, &c->lvl_tmp, &c->lvl_cnt,
@@ -911,9 +965,6 @@ int hermite_force_jerk_timed(hermite_ctx* c, const hermite_state* s, const hermi
     const hermite_tuning& tu = c->tuning[precision];
     CHECK(prepare_sweep(c, s, cl, s->xp, s->vp, idx, nullptr, n_act, eps2, precision, tu, acc,
                         jerk, pot, &a));
-    SweepArgs ra;
-    if (a.refine) CHECK(prepare_refine(c, a, &ra));
-    const int grid = std::max(1, c->n_cu * tu.wg_per_cu);
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     int rc = HERMITE_OK;
     double sum[4] = {0.0, 0.0, 0.0, 0.0};
@@ -921,9 +972,10 @@ int hermite_force_jerk_timed(hermite_ctx* c, const hermite_state* s, const hermi
         if (hipEventCreate(&ev[k]) != hipSuccess) rc = fail(HERMITE_EHIP, "hipEventCreate failed");
     for (int r = 0; r < reps && rc == HERMITE_OK; ++r) {
         hipError_t e = hipEventRecord(ev[0], st);
-        if (e == hipSuccess)
-            e = launch_force(a, a.refine ? &ra : nullptr, precision, tu.variant, grid, false, st,
-                             ev + 1);
+        if (e == hipSuccess) {
+            rc = run_force(c, a, precision, tu, false, st, ev + 1);
+            if (rc != HERMITE_OK) break;
+        }
         if (e == hipSuccess) e = hipEventRecord(ev[3], st);
         if (e == hipSuccess) e = hipEventSynchronize(ev[3]);
         float ms[3] = {0.f, 0.f, 0.f};
@@ -977,6 +1029,12 @@ int hermite_force_jerk_noalloc(const hermite_state* s, const hermite_clusters* c
     fill_sweep(sc, s, cl, s->xp, s->vp, idx, n_act_dev, n_act_max, eps2, precision, tu,
                default_near_factor(precision), default_fp64_below(precision),
                default_fp64_inter_below(precision), nullptr, acc, jerk, pot, &a);
+    PairShape sh;
+    if (pairs_fit(a, precision, nd->n_cu, false, &sh) &&
+        pair_partial_doubles(sh, a.n, a.n_cmax, false) <= sc.partial_cap) {
+        HIP_OK(launch_pairs(a, sh, (uint32_t*)sc.rplan, nd->n_cu, false, (hipStream_t)stream));
+        return HERMITE_OK;
+    }
     if (a.refine) fill_refine(sc, a, &ra);
     const int grid = std::max(1, nd->n_cu * tu.wg_per_cu);
     HIP_OK(launch_force(a, a.refine ? &ra : nullptr, precision, tu.variant, grid, false,
