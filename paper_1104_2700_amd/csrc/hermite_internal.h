@@ -66,6 +66,19 @@ struct SweepArgs {
     int32_t target_lanes;
     int32_t min_j_per_lane;
     int32_t ipl;               // active particles per lane (set by launch_force)
+    // One system whose active count the host knows: the plan, made there
+    // (host_plan nonzero; *plan is then neither written nor read, no plan
+    // kernel runs, and the reduce stage counts the interactions).
+    int32_t host_plan;
+    SweepPlan hp;
+    // The tuning is the default one: one system's split is chosen for its
+    // sizes (split_for_sizes) from the kernel's cost per pair and its
+    // resident workgroups per compute unit.
+    int32_t auto_split;
+    int32_t n_cu;
+    int32_t split_fp64;        // the sweep is FP64
+    int32_t split_res;
+    float split_cyc;
     int32_t one_chunk;         // nonzero: no j-split across work items (the
                                // paper-faithful mode's FP32 jerk sums span all j)
     // mixed precisions: pairs closer than near_factor * N_c^(-1/3) (N_c the
@@ -150,6 +163,14 @@ inline int reduce_grid(int64_t n_act_max)
 hipError_t launch_force(const SweepArgs& a, const SweepArgs* ra, int precision, int variant,
                         int grid, bool pot_only, hipStream_t st,
                         const hipEvent_t* marks = nullptr);
+
+// Sets the split model's kernel figures (split_*) of a sweep.
+void set_split_model(SweepArgs* a, int precision, int variant, bool pot_only);
+
+// The plan launch_force makes on the host for a sweep of one system whose
+// active count the host knows (a->n_clusters == 1, no n_act_dev; a->ipl set).
+// Returns whether the sweep is done in FP64.
+bool make_host_plan(SweepArgs* a, int precision, int variant, bool pot_only);
 
 // Block-step form of the refinement: the flagging reduce into the compact
 // outputs a.acc / a.jerk / a.pot, then the FP64 refine sweep (the corrector,

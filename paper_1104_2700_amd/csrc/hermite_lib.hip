@@ -271,7 +271,7 @@ bool uses_refine(int precision, int64_t n_cmax, int64_t fp64_below)
 
 // Fills the sweep arguments from a state, launch shape, mixed policy and
 // scratch (no allocation).
-void fill_sweep(const SweepScratch& sc, const hermite_state* s, const hermite_clusters* cl,
+void fill_sweep(const SweepScratch& sc, int n_cu, const hermite_state* s, const hermite_clusters* cl,
                 const double* xp, const double* vp, const int32_t* idx,
                 const int32_t* n_act_dev, int32_t n_act_max, double eps2, int precision,
                 const hermite_tuning& tu, double near_factor, int64_t fp64_below,
@@ -300,6 +300,15 @@ void fill_sweep(const SweepScratch& sc, const hermite_state* s, const hermite_cl
     a->partial_cap = sc.partial_cap;
     a->target_lanes = tu.target_lanes;
     a->min_j_per_lane = tu.min_j_per_lane;
+    a->n_cu = n_cu;
+    const hermite_tuning def = default_tuning_for(n_cu);
+    a->auto_split = std::memcmp(&tu, &def, sizeof def) == 0 ? 1 : 0;
+    if (a->auto_split && !cl) {
+        const bool mixed = precision == HERMITE_MIXED || precision == HERMITE_MIXED_2F;
+        const bool small = mixed && s->n < fp64_below;   // swept in FP64
+        set_split_model(a, small ? HERMITE_FP64 : precision, small ? tu.variant & 1 : tu.variant,
+                        false);
+    }
     a->near_factor = precision == HERMITE_FP64 ? 0.0 : near_factor;
     a->fp64_below = precision == HERMITE_FP64 ? 0 : fp64_below;
     a->fp64_inter_below =
@@ -324,7 +333,7 @@ void fill_sweep(const SweepScratch& sc, const hermite_state* s, const hermite_cl
 // and prediction, the flagged particles (ref_idx) as its active list, and
 // scratch of its own (its plan is made on the device after the flagging
 // reduce).
-void fill_refine(const SweepScratch& sc, const SweepArgs& a, SweepArgs* ra)
+void fill_refine(const SweepScratch& sc, const SweepArgs& a, int variant, SweepArgs* ra)
 {
     *ra = a;
     ra->idx = a.ref_idx;
@@ -344,6 +353,7 @@ void fill_refine(const SweepScratch& sc, const SweepArgs& a, SweepArgs* ra)
     ra->partial_cap = sc.partial_cap;
     ra->refine = 0;
     ra->defer_fp64 = 0;
+    if (ra->auto_split && ra->n_clusters == 1) set_split_model(ra, HERMITE_FP64, variant & 1, false);
     ra->near_factor = 0.0;
     ra->fp64_below = 0;
     ra->fp64_inter_below = 0;
@@ -417,18 +427,18 @@ int prepare_sweep(hermite_ctx* c, const hermite_state* s, const hermite_clusters
     SweepScratch sc;
     CHECK(ctx_scratch(c, C, n_act_max, refine, &sc));
     CHECK(ensure(c, c->counters, sizeof(int64_t) * kCounters));
-    fill_sweep(sc, s, cl, xp, vp, idx, n_act_dev, n_act_max, eps2, precision, tu, nfac, f64b,
+    fill_sweep(sc, c->n_cu, s, cl, xp, vp, idx, n_act_dev, n_act_max, eps2, precision, tu, nfac, f64b,
                c->fp64_inter_below[precision], (int64_t*)c->counters.p, acc, jerk, pot, a);
     return HERMITE_OK;
 }
 
 // The refine sweep's arguments from the context scratch (which
 // prepare_sweep has made for a refining sweep).
-int prepare_refine(hermite_ctx* c, const SweepArgs& a, SweepArgs* ra)
+int prepare_refine(hermite_ctx* c, const SweepArgs& a, int variant, SweepArgs* ra)
 {
     SweepScratch sc;
     CHECK(ctx_scratch(c, a.n_clusters, a.n_act_max, true, &sc));
-    fill_refine(sc, a, ra);
+    fill_refine(sc, a, variant, ra);
     return HERMITE_OK;
 }
 
@@ -489,7 +499,7 @@ int run_force(hermite_ctx* c, const SweepArgs& a, int precision, const hermite_t
     }
     const int grid = std::max(1, c->n_cu * tu.wg_per_cu);
     SweepArgs ra;
-    if (a.refine && !pot_only) CHECK(prepare_refine(c, a, &ra));
+    if (a.refine && !pot_only) CHECK(prepare_refine(c, a, tu.variant, &ra));
     HIP_OK(launch_force(a, (a.refine && !pot_only) ? &ra : nullptr, precision, tu.variant, grid,
                         pot_only, st, marks));
     return HERMITE_OK;
@@ -689,7 +699,7 @@ int enqueue_step(hermite_ctx* c, const hermite_state* s, const hermite_clusters*
         // mixed sums into the compact outputs with their error flags, the
         // FP64 refine sweep of the flagged particles, then the corrector
         SweepArgs ra;
-        CHECK(prepare_refine(c, a, &ra));
+        CHECK(prepare_refine(c, a, tu.variant, &ra));
         HIP_OK(launch_reduce_refine(a, ra, tu.variant, grid, st));
         ca.acc1 = out;
         ca.jrk1 = out + 3 * n;
@@ -1026,7 +1036,7 @@ int hermite_force_jerk_noalloc(const hermite_state* s, const hermite_clusters* c
     const SweepScratch sc = noalloc_carve(nd->base);
     const hermite_tuning tu = default_tuning_for(nd->n_cu);
     SweepArgs a, ra;
-    fill_sweep(sc, s, cl, s->xp, s->vp, idx, n_act_dev, n_act_max, eps2, precision, tu,
+    fill_sweep(sc, nd->n_cu, s, cl, s->xp, s->vp, idx, n_act_dev, n_act_max, eps2, precision, tu,
                default_near_factor(precision), default_fp64_below(precision),
                default_fp64_inter_below(precision), nullptr, acc, jerk, pot, &a);
     PairShape sh;
@@ -1035,7 +1045,7 @@ int hermite_force_jerk_noalloc(const hermite_state* s, const hermite_clusters* c
         HIP_OK(launch_pairs(a, sh, (uint32_t*)sc.rplan, nd->n_cu, false, (hipStream_t)stream));
         return HERMITE_OK;
     }
-    if (a.refine) fill_refine(sc, a, &ra);
+    if (a.refine) fill_refine(sc, a, tu.variant, &ra);
     const int grid = std::max(1, nd->n_cu * tu.wg_per_cu);
     HIP_OK(launch_force(a, a.refine ? &ra : nullptr, precision, tu.variant, grid, false,
                         (hipStream_t)stream));
@@ -1175,7 +1185,7 @@ static int launch_steps(hermite_ctx* c, const hermite_state* s, const hermite_cl
                             (int32_t*)c->step_na.p, (int32_t)s->n, eps2, precision,
                             c->tuning[precision], out, out + 3 * s->n, out + 6 * s->n, &a));
         SweepArgs ra;
-        if (a.refine) CHECK(prepare_refine(c, a, &ra));
+        if (a.refine) CHECK(prepare_refine(c, a, c->tuning[precision].variant, &ra));
     }
     hipStream_t st = (hipStream_t)stream;
     if (!use_graph) {
@@ -1639,7 +1649,15 @@ int hermite_autotune(hermite_ctx* c, const hermite_state* s, const hermite_clust
         rc = run(best, 1, &us, nullptr);
         if (rc != HERMITE_OK) break;
         SweepPlan P;
-        if (hipMemcpy(&P, c->plan.p, sizeof P, hipMemcpyDeviceToHost) != hipSuccess) {
+        if (!cl) {
+            SweepArgs a;
+            rc = prepare_sweep(c, s, cl, s->xp, s->vp, idx, nullptr, n_act, eps2, precision, best,
+                               out, out + 3 * (size_t)n_act, out + 6 * (size_t)n_act, &a);
+            if (rc != HERMITE_OK) break;
+            a.ipl = (best.variant & 1) ? 2 : 1;
+            (void)make_host_plan(&a, precision, best.variant, false);
+            P = a.hp;
+        } else if (hipMemcpy(&P, c->plan.p, sizeof P, hipMemcpyDeviceToHost) != hipSuccess) {
             rc = fail(HERMITE_EHIP, "reading the sweep plan failed");
             break;
         }

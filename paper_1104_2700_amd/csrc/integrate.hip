@@ -1017,7 +1017,7 @@ __device__ __forceinline__ FirstPos first_pos(const CorrectArgs& c, const SweepA
 
 __device__ __forceinline__ int first_chunks(const SweepArgs& sa, const FirstPos& f, int p)
 {
-    return (p == f.p && f.cl >= 0) ? sa.chunks[f.cl] : chunks_of(sa, p);
+    return (p == f.p && f.cl >= 0) ? sa.chunks[f.cl] : chunks_of(sa, sa.plan->s_max, p);
 }
 
 __device__ void correct_reduce_body(const CorrectArgs& c, const SweepArgs& sa, int na,
@@ -1081,7 +1081,6 @@ __global__ void __launch_bounds__(kWG) correct_refine_kernel(CorrectArgs c, Swee
     if (c.na_seen && blockIdx.x == 0 && threadIdx.x == 0) *c.na_seen = na;
     const int64_t T = c.T_dev ? *c.T_dev : c.T_host;
     const int64_t st = c.n_act_max;
-    const int cnt = ra.plan->n_act;
     const int lane = threadIdx.x & 63;
     // rounds of whole waves: a flagged lane's refine chunks are summed by
     // its wave together
@@ -1106,7 +1105,7 @@ __global__ void __launch_bounds__(kWG) correct_refine_kernel(CorrectArgs c, Swee
             fl &= fl - 1;
             const int kf = __shfl(k, owner);
             double s[kRows];
-            reduce_partials_wave(ra, cnt, kf, lane, s);
+            reduce_partials_wave(ra, *ra.plan, kf, lane, s);
             if (lane == owner) {
                 a1[0] = s[0]; a1[1] = s[1]; a1[2] = s[2];
                 j1[0] = s[3]; j1[1] = s[4]; j1[2] = s[5];

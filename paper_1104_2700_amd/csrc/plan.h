@@ -336,6 +336,130 @@ __device__ inline void plan_split_wave(const SweepArgs& a, int32_t na, int64_t c
     *jc_out = (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
 }
 
+// Chunk counts above kWaveReduceChunks use the wave-per-particle
+// reduction, unless the active block is large enough that one thread per
+// particle already fills the chip: then the thread form, whose loads are
+// coalesced over particles, is the faster one.
+constexpr int kWaveReduceChunks = 16;
+constexpr int kThreadReduceMinAct = 16384;
+
+__host__ __device__ __forceinline__ bool thread_reduce(int s_max, int na)
+{
+    return s_max <= kWaveReduceChunks || na >= kThreadReduceMinAct;
+}
+
+// A model of a sweep's time (microseconds) for na active particles of one
+// system, L lanes a particle and about items_want work items; *jc gets the
+// chunk length.  A tile costs a wave (kTJ / L) ipl pair evaluations of
+// split_cyc cycles and about 800 more (two barriers, the staging); split_res
+// workgroups share a compute unit, and a unit with only q of them left
+// advances like (q + rest[q]) / split_res of a full one; the 3 % are the
+// uneven finish of the last round; then the partial sums' way through the
+// reduction.  It balances items that fill the last round of resident
+// workgroups against rounds so short that a thin last one costs little.
+// (N = 65536, chunks x lanes, plan_split's / this choice: 3001 active mixed
+// 26 x 8 250 us / 43 x 8 226; FP64 43 x 8 259 / 32 x 4 254; 333 active FP64
+// 128 x 8 both; 65536 active mixed 10 x 1 4.11 / 16 x 1 3.90 ms; N = 16384,
+// 3000 active FP64 85 / 73.)
+__host__ __device__ inline float split_cost(const SweepArgs& a, int32_t na, int32_t L,
+                                            int64_t items_want, int64_t* jc)
+{
+#pragma clang fp contract(off)   // the host and the device choose alike
+    const int64_t T = (a.n + kTJ - 1) / kTJ;
+    const int64_t ti = (int64_t)a.ipl * (kWG / L);
+    int64_t max_ch = a.one_chunk ? 1 : div_floor(a.partial_cap, kRows * (int64_t)na);
+    if (max_ch > T) max_ch = T;
+    const int64_t tiles = div_ceil_p2(na, ti);
+    int64_t ch = div_floor(items_want, tiles);
+    if (ch > max_ch) ch = max_ch;
+    if (ch < 1) ch = 1;
+    const int64_t jt = div_ceil(T, ch);
+    ch = div_ceil(T, jt);
+    *jc = jt * kTJ;
+    const int64_t R = (int64_t)a.n_cu * a.split_res;
+    const int64_t items = tiles * ch, full = div_floor(items, R), rem = items - full * R;
+    const int q = (int)div_ceil(rem, a.n_cu);
+    const float rest = q == 0 ? 0.0f
+                     : a.split_fp64 ? (q == 1 ? 0.27f : q == 2 ? 0.10f : 0.0f)
+                                    : (q == 1 ? 0.84f : q == 2 ? 0.40f : q == 3 ? 0.24f : 0.0f);
+    const float part = ((float)q + rest) / (float)a.split_res;
+    const float rounds = (float)full + (part < 1.0f ? part : 1.0f);
+    const float wave = (float)(kTJ / L * a.ipl) * a.split_cyc + 800.0f;
+    const float even = 1.0f + 0.03f / (rounds > 1.0f ? rounds : 1.0f);
+    return even * rounds * (float)jt * wave * (float)a.split_res * (1.0f / 2100.0f) +
+           0.5f * (float)(full + (rem ? 1 : 0)) +
+           (float)(ch * na) * (float)(kRows * 8) *
+               (thread_reduce((int)ch, na) ? 1.0f / 1.2e6f : 1.0f / 0.8e6f);
+}
+
+// Candidate k of a split: a compute unit's worth of items (k < 4: k + 1
+// workgroups a unit, where that many fit), or k - 3 full rounds.
+constexpr int kSplitCands = 8;
+__host__ __device__ inline int64_t split_items(const SweepArgs& a, int k)
+{
+    return (int64_t)a.n_cu * (k < 4 ? (k + 1 < a.split_res ? k + 1 : a.split_res)
+                                    : (k - 3) * a.split_res);
+}
+
+// FP64 sweeps may take any number of lanes whose tiles are not mostly
+// empty; the mixed modes keep plan_split's (*L), which their FP32 runs follow.
+__host__ __device__ inline bool split_lanes_ok(const SweepArgs& a, int32_t na, int32_t L,
+                                               int32_t L_plan)
+{
+    if (!a.split_fp64) return L == L_plan;
+    return L == 64 || (int64_t)a.ipl * (kWG / L) <= 2 * (int64_t)na;
+}
+
+// The split of least modelled time (host).
+inline void split_for_sizes(const SweepArgs& a, int32_t na, int32_t* L_io, int64_t* jc_io)
+{
+    const int32_t L_plan = *L_io;
+    float best = 3.0e38f;
+    for (int32_t L = 1; L <= 64; L <<= 1) {
+        if (!split_lanes_ok(a, na, L, L_plan)) continue;
+        for (int k = 0; k < kSplitCands; ++k) {
+            int64_t jc;
+            const float t = split_cost(a, na, L, split_items(a, k), &jc);
+            if (t < best) {
+                best = t;
+                *L_io = L;
+                *jc_io = jc;
+            }
+        }
+    }
+}
+
+// Blocks of fewer interactions keep plan_split's choice: they are bound by
+// latency whatever their split (from 1e6 on / from 5e6 on: 40 of 65536
+// particles 19.0 / 22.1 us, 100 of 16384 12.8 / 15.8, 2000 of 2000 15.2 /
+// 18.9; 1024 of 1024 12.6 / 11.9).
+constexpr int64_t kSplitMinInter = 1000000;
+
+// The same by a wave (every lane calls it): lane 8 l + k takes 2^l lanes and
+// candidate k, and the first lane of least time wins, as above.
+__device__ inline void split_for_sizes_wave(const SweepArgs& a, int32_t na, int32_t* L_io,
+                                            int32_t* ti_out, int64_t* jc_io)
+{
+    const int lane = threadIdx.x & 63;
+    const int32_t L = 1 << (lane / kSplitCands < 6 ? lane / kSplitCands : 6);
+    int64_t jc;
+    float t = split_cost(a, na, L, split_items(a, lane % kSplitCands), &jc);
+    if (lane >= 7 * kSplitCands || !split_lanes_ok(a, na, L, *L_io)) t = 3.0e38f;
+    float m = t, u;
+    u = lane_partner<1>(m);  m = u < m ? u : m;
+    u = lane_partner<2>(m);  m = u < m ? u : m;
+    u = lane_partner<4>(m);  m = u < m ? u : m;
+    u = lane_partner<8>(m);  m = u < m ? u : m;
+    u = lane_partner<16>(m); m = u < m ? u : m;
+    u = lane_partner<32>(m); m = u < m ? u : m;
+    const int w = __builtin_ctzll(__ballot(t == m) | (1ull << 63));
+    const int lo = __builtin_amdgcn_readlane((int)jc, w);
+    const int hi = __builtin_amdgcn_readlane((int)(jc >> 32), w);
+    *L_io = __builtin_amdgcn_readlane(L, w);
+    *ti_out = a.ipl * (kWG / *L_io);
+    *jc_io = (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
+}
+
 __device__ inline int32_t block_exscan(int32_t v, int32_t* total)
 {
     __shared__ int32_t s_w[kWG / 64];
@@ -406,6 +530,8 @@ __device__ inline void plan_body(const SweepArgs& a, int32_t na_in,
         int32_t L, ti;
         int64_t jc;
         plan_split_wave(a, na, 1, &L, &ti, &jc);
+        if (a.auto_split && (int64_t)na * a.n >= kSplitMinInter)
+            split_for_sizes_wave(a, na, &L, &ti, &jc);
         if (tid == 0) {
             const int32_t tiles = (int32_t)div_ceil_p2(na, ti);
             const int32_t ch = na > 0 ? (int32_t)div_ceil(a.n, jc) : 0;
@@ -550,10 +676,29 @@ __device__ __forceinline__ void unpack_est(double d, float* ea, float* ej)
 // a sum that started at +0.0 unchanged bit for bit).
 constexpr int kReduceBatch = 4;
 
-// j-chunks of active position p (its cluster's).
-__device__ inline int chunks_of(const SweepArgs& a, int p)
+// The sweep's plan: the host's (HOST), or the one the plan stage left on the
+// device.  Fixed per kernel: a test of host_plan at run time puts its load
+// in front of the plan's (0.8 us of a 23 us block step).
+template <bool HOST>
+__device__ __forceinline__ const SweepPlan& plan_of(const SweepArgs& a)
 {
-    return a.n_clusters <= 1 ? a.plan->s_max : a.chunks[cluster_of(a, p)];
+    if constexpr (HOST) return a.hp;
+    else return *a.plan;
+}
+
+// j-chunks of active position p (its cluster's); s_max: the plan's.
+__device__ inline int chunks_of(const SweepArgs& a, int s_max, int p)
+{
+    return a.n_clusters <= 1 ? s_max : a.chunks[cluster_of(a, p)];
+}
+
+// With a host-made plan the reduce stage adds the sweep's interactions to
+// the counters (one thread of the grid).
+__device__ __forceinline__ void count_host_plan(const SweepArgs& a)
+{
+    if (a.host_plan && a.counters && blockIdx.x == 0 && threadIdx.x == 0)
+        atomicAdd((unsigned long long*)&a.counters[1],
+                  (unsigned long long)((int64_t)a.hp.n_act * a.n));
 }
 
 __device__ inline void reduce_partials_ch(const SweepArgs& a, int na, int p, int ch,
@@ -596,9 +741,10 @@ __device__ __forceinline__ void wave_sum_step(double* out, float& ea, float& ej)
 // The same sum by a whole wave (for many chunks): lane l adds chunks
 // l, l + 64, ... in order, then a fixed xor butterfly combines the lanes.
 // Every lane returns the total.  Deterministic for a given chunk count.
-__device__ inline void reduce_partials(const SweepArgs& a, int na, int p, double out[kRows])
+__device__ inline void reduce_partials(const SweepArgs& a, const SweepPlan& pl, int p,
+                                       double out[kRows])
 {
-    reduce_partials_ch(a, na, p, chunks_of(a, p), out);
+    reduce_partials_ch(a, pl.n_act, p, chunks_of(a, pl.s_max, p), out);
 }
 
 __device__ inline void reduce_partials_wave_ch(const SweepArgs& a, int na, int p, int ch,
@@ -626,10 +772,10 @@ __device__ inline void reduce_partials_wave_ch(const SweepArgs& a, int na, int p
     out[kRows - 1] = pack_est(ea, ej);
 }
 
-__device__ inline void reduce_partials_wave(const SweepArgs& a, int na, int p, int lane,
-                                            double out[kRows])
+__device__ inline void reduce_partials_wave(const SweepArgs& a, const SweepPlan& pl, int p,
+                                            int lane, double out[kRows])
 {
-    reduce_partials_wave_ch(a, na, p, chunks_of(a, p), lane, out);
+    reduce_partials_wave_ch(a, pl.n_act, p, chunks_of(a, pl.s_max, p), lane, out);
 }
 
 // Position and velocity of particle i for the sweep: predicted on the fly
@@ -655,18 +801,6 @@ __device__ inline void fetch_particle(const SweepArgs& a, int64_t i, int64_t T, 
             w[d] = a.vp[d * n + i];
         }
     }
-}
-
-// Chunk counts above kWaveReduceChunks use the wave-per-particle
-// reduction, unless the active block is large enough that one thread per
-// particle already fills the chip: then the thread form, whose loads are
-// coalesced over particles, is the faster one.
-constexpr int kWaveReduceChunks = 16;
-constexpr int kThreadReduceMinAct = 16384;
-
-__device__ __forceinline__ bool thread_reduce(int s_max, int na)
-{
-    return s_max <= kWaveReduceChunks || na >= kThreadReduceMinAct;
 }
 
 // ------------------------------------------------------------------------

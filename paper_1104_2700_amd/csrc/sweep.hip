@@ -41,6 +41,8 @@
 #include "hermite_internal.h"
 #include "plan.h"
 
+#include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 namespace hm {
@@ -782,7 +784,9 @@ constexpr int sweep_min_waves()
            : (SPLIT && PREC == 1) ? 3 : 1;
 }
 
-template <int PREC, bool POT_ONLY, int IPL, bool SPLIT, bool SEL = false, int KR = kMixedK>
+// HOST: the plan is the host's (SweepArgs::hp).
+template <int PREC, bool POT_ONLY, int IPL, bool SPLIT, bool SEL = false, int KR = kMixedK,
+          bool HOST = false>
 __global__ void __launch_bounds__(kWG, (sweep_min_waves<PREC, IPL, SPLIT, SEL>()))
 sweep_kernel(SweepArgs a)
 {
@@ -845,13 +849,14 @@ sweep_kernel(SweepArgs a)
             }
         }
     } else {
-        na = P->n_act;
-        L = P->L;
-        ti = P->ti;
-        jc = P->jc;
-        s_max = P->s_max;
-        total = P->total_items;
-        fp64_all = P->fp64_all;
+        const SweepPlan& pl = plan_of<HOST>(a);
+        na = pl.n_act;
+        L = pl.L;
+        ti = pl.ti;
+        jc = pl.jc;
+        s_max = pl.s_max;
+        total = pl.total_items;
+        fp64_all = pl.fp64_all;
         Tpred = a.pred_x ? *a.pred_T : 0;
     }
     if (na == 0) return;
@@ -1101,14 +1106,16 @@ __device__ __forceinline__ void store_reduced(const SweepArgs& a, int p, const d
     if (a.pot) a.pot[p] = s[6];
 }
 
-template <bool POT_ONLY>
+template <bool POT_ONLY, bool HOST>
 __global__ void __launch_bounds__(kWG) reduce_kernel(SweepArgs a)
 {
-    const int na = a.plan->n_act;
-    if (thread_reduce(a.plan->s_max, na)) {
+    const SweepPlan pl = plan_of<HOST>(a);
+    const int na = pl.n_act;
+    count_host_plan(a);
+    if (thread_reduce(pl.s_max, na)) {
         for (int p = blockIdx.x * kWG + threadIdx.x; p < na; p += gridDim.x * kWG) {
             double s[kRows];
-            reduce_partials(a, na, p, s);
+            reduce_partials(a, pl, p, s);
             store_reduced<POT_ONLY>(a, p, s);
         }
     } else {
@@ -1116,7 +1123,7 @@ __global__ void __launch_bounds__(kWG) reduce_kernel(SweepArgs a)
         const int wpb = kWG / 64;
         for (int p = blockIdx.x * wpb + (int)(threadIdx.x >> 6); p < na; p += gridDim.x * wpb) {
             double s[kRows];
-            reduce_partials_wave(a, na, p, lane, s);
+            reduce_partials_wave(a, pl, p, lane, s);
             if (lane == 0) store_reduced<POT_ONLY>(a, p, s);
         }
     }
@@ -1127,18 +1134,21 @@ __global__ void __launch_bounds__(kWG) reduce_kernel(SweepArgs a)
 // positions whose error estimate is too large; refine_plan_kernel then
 // lists them and plans the FP64 refine sweep.  Rounds run with uniform
 // trip counts over the workgroup (the compaction synchronises it).
+template <bool HOST>
 __global__ void __launch_bounds__(kWG) reduce_flag_kernel(SweepArgs a)
 {
-    if (a.defer_fp64 && a.plan->fp64_all) return;
-    const int na = a.plan->n_act;
-    if (thread_reduce(a.plan->s_max, na)) {
+    const SweepPlan pl = plan_of<HOST>(a);
+    if (a.defer_fp64 && pl.fp64_all) return;
+    const int na = pl.n_act;
+    count_host_plan(a);
+    if (thread_reduce(pl.s_max, na)) {
         for (int u = blockIdx.x; u * kWG < na; u += gridDim.x) {
             const int base = u * kWG;
             const int p = base + (int)threadIdx.x;
             bool flag = false;
             if (p < na) {
                 double s[kRows];
-                reduce_partials(a, na, p, s);
+                reduce_partials(a, pl, p, s);
                 store_reduced<false>(a, p, s);
                 flag = needs_refine(a, s);
             }
@@ -1153,7 +1163,7 @@ __global__ void __launch_bounds__(kWG) reduce_flag_kernel(SweepArgs a)
             bool flag = false;
             if (p < na) {
                 double s[kRows];
-                reduce_partials_wave(a, na, p, lane, s);
+                reduce_partials_wave(a, pl, p, lane, s);
                 if (lane == 0) store_reduced<false>(a, p, s);
                 flag = needs_refine(a, s);
             }
@@ -1163,12 +1173,14 @@ __global__ void __launch_bounds__(kWG) reduce_flag_kernel(SweepArgs a)
 }
 
 // One workgroup: the refine list and the plan of the refine sweep ra.
+template <bool HOST>
 __global__ void __launch_bounds__(kWG) refine_plan_kernel(SweepArgs a, SweepArgs ra)
 {
-    if (a.defer_fp64 && a.plan->fp64_all) {
+    const SweepPlan pl = plan_of<HOST>(a);
+    const int na = pl.n_act;
+    if (a.defer_fp64 && pl.fp64_all) {
         // an FP64 block: the refine sweep takes all of it, in list order
         // (its clusters' runs where the sweep's are)
-        const int na = a.plan->n_act;
         for (int k = threadIdx.x; k < na; k += kWG) {
             a.ref_idx[k] = a.idx ? a.idx[k] : k;
             a.ref_p[k] = k;
@@ -1179,8 +1191,7 @@ __global__ void __launch_bounds__(kWG) refine_plan_kernel(SweepArgs a, SweepArgs
         plan_body(ra, na);
         return;
     }
-    const int na = a.plan->n_act;
-    const int unit = thread_reduce(a.plan->s_max, na) ? kWG : kWG / 64;
+    const int unit = thread_reduce(pl.s_max, na) ? kWG : kWG / 64;
     const int32_t cnt = build_refine_list(a, ra, na, unit);
     if (threadIdx.x == 0 && a.counters && cnt > 0)
         atomicAdd((unsigned long long*)&a.counters[5], (unsigned long long)cnt);
@@ -1191,12 +1202,13 @@ __global__ void __launch_bounds__(kWG) refine_plan_kernel(SweepArgs a, SweepArgs
 // block the plan put in FP64 these are all of its particles.
 __global__ void __launch_bounds__(kWG) refine_scatter_kernel(SweepArgs a, SweepArgs ra)
 {
-    const int cnt = ra.plan->n_act;
+    const SweepPlan pl = *ra.plan;
+    const int cnt = pl.n_act;
     const int lane = threadIdx.x & 63;
     const int wpb = kWG / 64;
     for (int k = blockIdx.x * wpb + (int)(threadIdx.x >> 6); k < cnt; k += gridDim.x * wpb) {
         double s[kRows];
-        reduce_partials_wave(ra, cnt, k, lane, s);
+        reduce_partials_wave(ra, pl, k, lane, s);
         if (lane == 0) store_reduced<false>(a, a.ref_p[k], s);
     }
 }
@@ -1223,31 +1235,68 @@ SweepFn sweep_sel_fn(int precision, int variant)
 // variant: bit 0 -> two active particles per lane; bit 1 -> split
 // differences (MIXED and MIXED_2F only; FP64 and MIXED_SP ignore it); bit 2
 // -> FP32 runs of kMixedKLong (the mixed precisions; FP64 ignores it).
-template <int PREC, int IPL, bool SPLIT>
+template <int PREC, int IPL, bool SPLIT, bool HOST>
 SweepFn mixed_fn(bool long_runs)
 {
-    return long_runs ? sweep_kernel<PREC, false, IPL, SPLIT, false, kMixedKLong>
-                     : sweep_kernel<PREC, false, IPL, SPLIT, false, kMixedK>;
+    return long_runs ? sweep_kernel<PREC, false, IPL, SPLIT, false, kMixedKLong, HOST>
+                     : sweep_kernel<PREC, false, IPL, SPLIT, false, kMixedK, HOST>;
 }
 
-SweepFn sweep_fn(int precision, int variant, bool pot_only)
+template <bool HOST>
+SweepFn sweep_fn_of(int precision, int variant, bool pot_only)
 {
-    if (pot_only) return sweep_kernel<0, true, 1, false>;
+    if (pot_only) return sweep_kernel<0, true, 1, false, false, kMixedK, HOST>;
     const bool two = (variant & 1) != 0;
     const bool spl = (variant & 2) != 0;
     const bool lng = (variant & 4) != 0;
     if (precision == 0)
-        return two ? sweep_kernel<0, false, 2, false> : sweep_kernel<0, false, 1, false>;
+        return two ? sweep_kernel<0, false, 2, false, false, kMixedK, HOST>
+                   : sweep_kernel<0, false, 1, false, false, kMixedK, HOST>;
     if (precision == 1) {
-        if (spl) return two ? mixed_fn<1, 2, true>(lng) : mixed_fn<1, 1, true>(lng);
-        return two ? mixed_fn<1, 2, false>(lng) : mixed_fn<1, 1, false>(lng);
+        if (spl) return two ? mixed_fn<1, 2, true, HOST>(lng) : mixed_fn<1, 1, true, HOST>(lng);
+        return two ? mixed_fn<1, 2, false, HOST>(lng) : mixed_fn<1, 1, false, HOST>(lng);
     }
-    if (precision == 3) return two ? mixed_fn<3, 2, false>(lng) : mixed_fn<3, 1, false>(lng);
-    if (spl) return two ? mixed_fn<2, 2, true>(lng) : mixed_fn<2, 1, true>(lng);
-    return two ? mixed_fn<2, 2, false>(lng) : mixed_fn<2, 1, false>(lng);
+    if (precision == 3)
+        return two ? mixed_fn<3, 2, false, HOST>(lng) : mixed_fn<3, 1, false, HOST>(lng);
+    if (spl) return two ? mixed_fn<2, 2, true, HOST>(lng) : mixed_fn<2, 1, true, HOST>(lng);
+    return two ? mixed_fn<2, 2, false, HOST>(lng) : mixed_fn<2, 1, false, HOST>(lng);
+}
+
+SweepFn sweep_fn(int precision, int variant, bool pot_only, bool host_plan = false)
+{
+    return host_plan ? sweep_fn_of<true>(precision, variant, pot_only)
+                     : sweep_fn_of<false>(precision, variant, pot_only);
 }
 
 }  // namespace
+
+// Resident workgroups per compute unit of a sweep kernel (from its register
+// and LDS use), asked of the runtime once per kernel.
+int sweep_occupancy(int precision, int variant, bool pot_only)
+{
+    static std::atomic<int> known[4][8][2];
+    std::atomic<int>& k = known[precision][variant & 7][pot_only ? 1 : 0];
+    int nb = k.load(std::memory_order_relaxed);
+    if (nb > 0) return nb;
+    const void* f = reinterpret_cast<const void*>(sweep_fn(precision, variant, pot_only));
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kWG, 0) != hipSuccess || nb < 1) {
+        (void)hipGetLastError();
+        return 4;
+    }
+    k.store(nb, std::memory_order_relaxed);
+    return nb;
+}
+
+void set_split_model(SweepArgs* a, int precision, int variant, bool pot_only)
+{
+    // cycles of a SIMD per wave and pair: FP64 33 instructions of four
+    // cycles and v_rsq_f64 of 16; the mixed modes' FP64 differences and
+    // conversions of four, FP32 of two
+    static const float cyc[4] = {148.0f, 112.0f, 125.0f, 95.0f};
+    a->split_fp64 = precision == 0 ? 1 : 0;
+    a->split_cyc = pot_only ? 68.0f : cyc[precision];
+    a->split_res = sweep_occupancy(precision, variant, pot_only);
+}
 
 int max_plan_items(const SweepArgs& a)
 {
@@ -1277,13 +1326,16 @@ void launch_sweep_kernels(SweepArgs a, int precision, int variant, int grid, boo
     a.ipl = (!pot_only && (variant & 1)) ? 2 : 1;
     auto go = [&](int prec, int kind) {
         a.kind = kind;
-        SweepFn f = sel ? sweep_sel_fn(prec, variant) : sweep_fn(prec, variant, pot_only);
+        SweepFn f = sel ? sweep_sel_fn(prec, variant)
+                        : sweep_fn(prec, variant, pot_only, a.host_plan != 0);
         hipLaunchKernelGGL(f, dim3(grid), dim3(kWG), 0, st, a);
     };
     const bool mixed = !pot_only && (precision == 1 || precision == 2);
     const bool straddle = a.n_clusters > 1 && a.fp64_below > 1;
     if (!mixed) {
         go(precision, 0);
+    } else if (a.host_plan) {
+        go(a.n_cmax < a.fp64_below ? 0 : precision, 0);   // the host decided
     } else if (a.n_cmax < a.fp64_below) {
         go(0, 0);                          // every system is small
     } else if (straddle || (!sel && a.fp64_inter_below > 0)) {
@@ -1317,23 +1369,67 @@ hipError_t launch_reduce_refine(const SweepArgs& a_in, const SweepArgs& ra_in, i
 {
     SweepArgs a = a_in, ra = ra_in;
     a.ipl = ra.ipl = (variant & 1) ? 2 : 1;
-    hipLaunchKernelGGL(reduce_flag_kernel, dim3(reduce_grid(a.n_act_max)), dim3(kWG), 0, st, a);
-    hipLaunchKernelGGL(refine_plan_kernel, dim3(1), dim3(kWG), 0, st, a, ra);
+    const dim3 rgrid(reduce_grid(a.n_act_max));
+    if (a.host_plan) {
+        hipLaunchKernelGGL(reduce_flag_kernel<true>, rgrid, dim3(kWG), 0, st, a);
+        hipLaunchKernelGGL(refine_plan_kernel<true>, dim3(1), dim3(kWG), 0, st, a, ra);
+    } else {
+        hipLaunchKernelGGL(reduce_flag_kernel<false>, rgrid, dim3(kWG), 0, st, a);
+        hipLaunchKernelGGL(refine_plan_kernel<false>, dim3(1), dim3(kWG), 0, st, a, ra);
+    }
     // the FP64 kernel with the mixed variant's particles per lane (the plan
     // was made for that count)
     launch_sweep_kernels(ra, 0, variant & 1, grid, false, false, st);
     return hipGetLastError();
 }
 
+bool make_host_plan(SweepArgs* a, int precision, int variant, bool pot_only)
+{
+    const int32_t na = a->n_act_max;
+    const bool mixed = precision == 1 || precision == 2;
+    const bool small = mixed && a->fp64_inter_below > 0 && (int64_t)na * a->n < a->fp64_inter_below;
+    const bool fp64 = pot_only || precision == 0 || (mixed && (a->n < a->fp64_below || small));
+    int32_t L, ti;
+    int64_t jc;
+    plan_split(*a, na, 1, &L, &ti, &jc);
+    if (a->auto_split && (int64_t)na * a->n >= kSplitMinInter) {
+        if (fp64) set_split_model(a, 0, variant & 1, pot_only);
+        split_for_sizes(*a, na, &L, &jc);
+        ti = a->ipl * (kWG / L);
+    }
+    a->host_plan = 1;
+    a->hp.n_act = na;
+    a->hp.L = L;
+    a->hp.ti = ti;
+    a->hp.jc = jc;
+    a->hp.s_max = (int32_t)div_ceil(a->n, jc);
+    a->hp.total_items = (int32_t)div_ceil_p2(na, ti) * a->hp.s_max;
+    a->hp.fp64_all = mixed && fp64 ? 1 : 0;
+    return fp64;
+}
+
 hipError_t launch_force(const SweepArgs& a_in, const SweepArgs* ra, int precision, int variant,
                         int grid, bool pot_only, hipStream_t st, const hipEvent_t* marks)
 {
     SweepArgs a = a_in;
+    const int a_grid = grid;   // the refine sweep's: its count is the device's
     a.ipl = (!pot_only && (variant & 1)) ? 2 : 1;
+    bool refine = !pot_only && ra && a.refine;
+    if (a.n_clusters == 1 && !a.n_act_dev) {
+        const bool fp64 = make_host_plan(&a, precision, variant, pot_only);
+        if (fp64 && refine) {
+            // an FP64 block: the plain FP64 sweep and its reduction
+            precision = 0;
+            variant &= 1;
+            refine = false;
+            a.refine = 0;
+        }
+        if (a.hp.total_items < grid) grid = a.hp.total_items;
+    }
     // with refinement, a block the plan puts in FP64 is swept by the refine
     // sweep's launch (the whole block as its list) and scattered from there
-    a.defer_fp64 = (!pot_only && ra && a.refine) ? 1 : 0;
-    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kWG), 0, st, a);
+    a.defer_fp64 = refine ? 1 : 0;
+    if (!a.host_plan) hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kWG), 0, st, a);
     if (marks) {
         const hipError_t e = hipEventRecord(marks[0], st);
         if (e != hipSuccess) return e;
@@ -1344,35 +1440,24 @@ hipError_t launch_force(const SweepArgs& a_in, const SweepArgs* ra, int precisio
         if (e != hipSuccess) return e;
     }
     const int rgrid = reduce_grid(a.n_act_max);
+    auto reduce = [&](auto pot) {
+        if (a.host_plan)
+            hipLaunchKernelGGL((reduce_kernel<pot.value, true>), dim3(rgrid), dim3(kWG), 0, st, a);
+        else
+            hipLaunchKernelGGL((reduce_kernel<pot.value, false>), dim3(rgrid), dim3(kWG), 0, st, a);
+    };
     if (pot_only) {
-        hipLaunchKernelGGL(reduce_kernel<true>, dim3(rgrid), dim3(kWG), 0, st, a);
-    } else if (ra && a.refine) {
-        const hipError_t e = launch_reduce_refine(a, *ra, variant, grid, st);
+        reduce(std::true_type());
+    } else if (refine) {
+        const hipError_t e = launch_reduce_refine(a, *ra, variant, a_grid, st);
         if (e != hipSuccess) return e;
         SweepArgs r = *ra;
         r.ipl = a.ipl;
         hipLaunchKernelGGL(refine_scatter_kernel, dim3(rgrid), dim3(kWG), 0, st, a, r);
     } else {
-        hipLaunchKernelGGL(reduce_kernel<false>, dim3(rgrid), dim3(kWG), 0, st, a);
+        reduce(std::false_type());
     }
     return hipGetLastError();
-}
-
-}  // namespace hm
-
-namespace hm {
-
-// Resident workgroups per compute unit of a sweep kernel (from its register
-// and LDS use); the default persistent grid is this times the CU count.
-int sweep_occupancy(int precision, int variant, bool pot_only)
-{
-    int nb = 0;
-    const void* f = reinterpret_cast<const void*>(sweep_fn(precision, variant, pot_only));
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kWG, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        return 4;
-    }
-    return nb;
 }
 
 }  // namespace hm
