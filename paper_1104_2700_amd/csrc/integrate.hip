@@ -2,6 +2,7 @@
 // predictor, corrector + next timestep, first timestep, energy sums.
 // All are memory/latency bound; every thread handles whole particles and
 // reads/writes SoA arrays with unit stride.
+#include "correct.h"
 #include "hermite_internal.h"
 #include "plan.h"
 
@@ -402,11 +403,6 @@ __global__ void __launch_bounds__(kWG) sel_single_plan_kernel(
 }
 
 // ---- block selection from the step-size order (procedure step 1) ---------
-__device__ __forceinline__ int log2_step(int64_t dt)
-{
-    return 63 - __clzll((unsigned long long)dt);
-}
-
 // Step counts of the state and its consistency: every dt_i a power of two
 // no finer than dt_floor, t_i >= 0 a multiple of dt_i, and (checked on the
 // host) max t < min (t + dt).
@@ -857,44 +853,7 @@ __global__ void __launch_bounds__(kWG) predict_kernel(int64_t n, const int64_t* 
     predict_one(n, i, T, t, pa);
 }
 
-// ---- timestep: Aarseth criterion and power-of-two quantisation ----------
-__device__ __forceinline__ double norm3(double a, double b, double c)
-{
-    return sqrt(fma(a, a, fma(b, b, c * c)));
-}
-
-__device__ int64_t quantize_dt(double crit, int k_old, int64_t T, int tick_bits,
-                               int k_min, int k_max, int* clamped)
-{
-    int k;
-    *clamped = 0;
-    if (__builtin_isnan(crit) || __builtin_isinf(crit)) {
-        k = k_min;
-    } else if (crit <= 0.0) {
-        k = k_max;
-        *clamped = 1;
-    } else {
-        int e;
-        frexp(crit, &e);            // crit in [2^(e-1), 2^e)
-        k = 1 - e;
-        if (k < k_min) k = k_min;
-        if (k > k_max) { k = k_max; *clamped = 1; }
-    }
-    if (k_old >= 0 && k < k_old - 1) k = k_old - 1;
-    while (k < k_max && (T & ((((int64_t)1) << (tick_bits - k)) - 1)) != 0) ++k;
-    return ((int64_t)1) << (tick_bits - k);
-}
-
 // ---- corrector + next step (procedure steps 5-8) -------------------------
-// The pre-step state of an active particle that the corrector reads, loaded
-// before the new forces are summed so that these loads overlap the sum's.
-struct OldState {
-    int i;                      // particle index
-    int64_t t, dt;
-    double x[3], v[3];          // x, v (prediction in place) or xp, vp
-    double a[3], j[3];
-};
-
 __device__ __forceinline__ void load_old_i(const CorrectArgs& c, int i, OldState& o)
 {
     const int64_t n = c.n;
@@ -924,19 +883,9 @@ __device__ void correct_one(const CorrectArgs& c, int p, const OldState& o, int6
     const int64_t n = c.n;
     const int i = o.i;
     const double tick = ldexp(1.0, -c.tick_bits);
-    const int64_t dt_old = o.dt;
-    const double h = (double)dt_old * tick;
-    const double h2 = h * h, h3 = h2 * h, h4 = h3 * h, h5 = h4 * h;
-    double s1[3], cc[3], xp[3], vp[3];
+    double xp[3], vp[3];
     if (c.predict_i) {
-        // equations (xpred), (vpred) for this particle, dt = T - t_i
-        const double hp = (double)(T - o.t) * tick;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const double ac = o.a[d], jk = o.j[d];
-            xp[d] = fma(hp, fma(hp, fma(hp, jk * (1.0 / 6.0), ac * 0.5), o.v[d]), o.x[d]);
-            vp[d] = fma(hp, fma(hp, jk * 0.5, ac), o.v[d]);
-        }
+        predict_old(o, T, tick, xp, vp);
     } else {
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
@@ -944,36 +893,22 @@ __device__ void correct_one(const CorrectArgs& c, int p, const OldState& o, int6
             vp[d] = o.v[d];
         }
     }
+    Corrected r;
+    correct_core(o, xp, vp, T, tick, c.tick_bits, a1v, j1v, c.eta, c.form, c.k_min, c.k_max, &r);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         const int64_t q = d * n + i;
-        const double a0 = o.a[d], j0 = o.j[d];
-        const double a1 = a1v[d], j1 = j1v[d];
-        const double da = a0 - a1;
-        const double s0 = 2.0 * (-3.0 * da - (2.0 * j0 + j1) * h) / h2;
-        const double c0 = 6.0 * (2.0 * da + (j0 + j1) * h) / h3;
-        c.x[q] = xp[d] + s0 * h4 / 24.0 + c0 * h5 / 120.0;
-        c.v[q] = vp[d] + s0 * h3 / 6.0 + c0 * h4 / 24.0;
-        c.a[q] = a1;
-        c.j[q] = j1;
-        s1[d] = fma(c0, h, s0);
-        cc[d] = c0;
+        c.x[q] = r.x[d];
+        c.v[q] = r.v[d];
+        c.a[q] = a1v[d];
+        c.j[q] = j1v[d];
     }
     if (have_pot) c.pot[i] = pot1;
     c.t[i] = T;
-    const double A = norm3(a1v[0], a1v[1], a1v[2]);
-    const double J = norm3(j1v[0], j1v[1], j1v[2]);
-    const double S = norm3(s1[0], s1[1], s1[2]);
-    const double Cn = norm3(cc[0], cc[1], cc[2]);
-    const double R = (A * S + J * J) / (J * Cn + S * S);
-    const double crit = c.form == 0 ? c.eta * sqrt(R) : sqrt(c.eta * R);
-    if (c.crit_out) c.crit_out[p] = crit;
-    const int k_old = c.tick_bits - log2_step(dt_old);
-    int cl;
-    const int64_t dt_new = quantize_dt(crit, k_old, T, c.tick_bits, c.k_min, c.k_max, &cl);
-    c.dt[i] = dt_new;
-    if (c.lv_out) c.lv_out[p] = (uint8_t)log2_step(dt_new);
-    if (cl && c.counters) atomicAdd((unsigned long long*)&c.counters[2], 1ull);
+    if (c.crit_out) c.crit_out[p] = r.crit;
+    c.dt[i] = r.dt;
+    if (c.lv_out) c.lv_out[p] = (uint8_t)log2_step(r.dt);
+    if (r.clamped && c.counters) atomicAdd((unsigned long long*)&c.counters[2], 1ull);
 }
 
 __global__ void __launch_bounds__(kWG) correct_kernel(CorrectArgs c)

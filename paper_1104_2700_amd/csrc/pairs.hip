@@ -37,6 +37,7 @@
 // the item's: each particle has one value per chunk of its own row and one
 // per block that met it.  pair_reduce_kernel adds them in a fixed order.
 #include "hermite_internal.h"
+#include "pair.h"
 #include "plan.h"
 
 #include <algorithm>
@@ -45,15 +46,6 @@
 
 namespace hm {
 namespace {
-
-__device__ __forceinline__ double rsqrt_f64(double s)
-{
-    const double y = __builtin_amdgcn_rsq(s);
-    const double h = s * y;
-    const double e = fma(-h, y, 1.0);
-    const double p = fma(e, 0.375, 0.5);
-    return fma(y * e, p, y);
-}
 
 // Blocks of a system of nc particles and the j tiles of block a's row.
 __host__ __device__ inline int pair_blocks(int64_t nc, int bi)

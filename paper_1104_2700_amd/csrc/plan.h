@@ -8,99 +8,115 @@
 namespace hm {
 
 // ---- wave-level primitives (every lane of the wave must call them) ----
-// The partner's value in step O of a butterfly in which the lanes of each
-// aligned group of 2 O combine their values (every lane ends with the
-// group's result).  Within a 16-lane row the partner comes through a DPP
-// lane move: quad permutes for O = 1, 2, then the half-row and row mirrors
+// The two values that step O of a butterfly combines in each lane, in which
+// the lanes of each aligned group of 2 O combine theirs (every lane ends with
+// the group's result): the lane's own and its partner's, in either order (the
+// operation commutes).  Within a 16-lane row the partner's comes through a
+// DPP lane move: quad permutes for O = 1, 2, then the half-row and row mirrors
 // for O = 4, 8.  After the earlier steps all lanes of a quad (of a half-row)
 // hold the same value, so the mirror partner gives bit for bit the xor
-// partner's result (steps must run in ascending O).  Across rows (O = 16,
-// 32) the value goes through ds_bpermute.
+// partner's result (steps must run in ascending O).  Across rows (O = 16, 32)
+// a lane swap of the value with itself leaves the lower rows' values in one
+// register and the upper rows' in the other, one instruction a word where
+// ds_bpermute goes through the LDS unit.
 template <int O>
-__device__ __forceinline__ int lane_partner_i32(int v)
+__device__ __forceinline__ void lane_both(int32_t v, int32_t& a, int32_t& b)
 {
-    static_assert(O == 1 || O == 2 || O == 4 || O == 8, "DPP steps");
-    constexpr int kCtrl = O == 1 ? 0xB1 : O == 2 ? 0x4E : O == 4 ? 0x141 : 0x140;
-    return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xF, 0xF, false);
-}
-
-template <int O>
-__device__ __forceinline__ int32_t lane_xor(int32_t v)
-{
-    if constexpr (O >= 16) return __shfl_xor(v, O);
-    else return lane_partner_i32<O>(v);
-}
-
-template <int O>
-__device__ __forceinline__ int64_t lane_xor(int64_t v)
-{
-    if constexpr (O >= 16) {
-        return __shfl_xor(v, O);
+    static_assert(O == 1 || O == 2 || O == 4 || O == 8 || O == 16 || O == 32, "butterfly steps");
+    if constexpr (O == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+        a = (int32_t)r[0];
+        b = (int32_t)r[1];
+    } else if constexpr (O == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+        a = (int32_t)r[0];
+        b = (int32_t)r[1];
     } else {
-        const int lo = lane_partner_i32<O>((int)v);
-        const int hi = lane_partner_i32<O>((int)(v >> 32));
-        return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
+        constexpr int kCtrl = O == 1 ? 0xB1 : O == 2 ? 0x4E : O == 4 ? 0x141 : 0x140;
+        a = v;
+        b = __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xF, 0xF, false);
     }
 }
 
 template <int O>
-__device__ __forceinline__ double lane_partner(double v)
+__device__ __forceinline__ void lane_both(int64_t v, int64_t& a, int64_t& b)
 {
-    return __longlong_as_double((long long)lane_xor<O>((int64_t)__double_as_longlong(v)));
+    int32_t al, ah, bl, bh;
+    lane_both<O>((int32_t)v, al, bl);
+    lane_both<O>((int32_t)(v >> 32), ah, bh);
+    a = (int64_t)(((uint64_t)(uint32_t)ah << 32) | (uint64_t)(uint32_t)al);
+    b = (int64_t)(((uint64_t)(uint32_t)bh << 32) | (uint64_t)(uint32_t)bl);
+}
+
+// Step O of a sum.
+template <int O>
+__device__ __forceinline__ double lane_sum(double v)
+{
+    int64_t a, b;
+    lane_both<O>((int64_t)__double_as_longlong(v), a, b);
+    return __longlong_as_double((long long)a) + __longlong_as_double((long long)b);
 }
 
 template <int O>
-__device__ __forceinline__ float lane_partner(float v)
+__device__ __forceinline__ float lane_sum(float v)
 {
-    return __int_as_float(lane_xor<O>((int32_t)__float_as_int(v)));
+    int32_t a, b;
+    lane_both<O>((int32_t)__float_as_int(v), a, b);
+    return __int_as_float(a) + __int_as_float(b);
 }
 
-__device__ __forceinline__ int32_t wave_sum_i32(int32_t v)
+template <int O, typename T>
+__device__ __forceinline__ T lane_sum(T v)
 {
-    v += lane_xor<1>(v);
-    v += lane_xor<2>(v);
-    v += lane_xor<4>(v);
-    v += lane_xor<8>(v);
-    v += lane_xor<16>(v);
-    v += lane_xor<32>(v);
-    return v;
+    T a, b;
+    lane_both<O>(v, a, b);
+    return a + b;
 }
 
-__device__ __forceinline__ int64_t wave_sum_i64(int64_t v)
+template <int O, typename T>
+__device__ __forceinline__ T lane_min(T v)
 {
-    v += lane_xor<1>(v);
-    v += lane_xor<2>(v);
-    v += lane_xor<4>(v);
-    v += lane_xor<8>(v);
-    v += lane_xor<16>(v);
-    v += lane_xor<32>(v);
-    return v;
+    T a, b;
+    lane_both<O>(v, a, b);
+    return b < a ? b : a;
 }
 
+template <int O>
+__device__ __forceinline__ float lane_min(float v)
+{
+    int32_t a, b;
+    lane_both<O>((int32_t)__float_as_int(v), a, b);
+    const float x = __int_as_float(a), y = __int_as_float(b);
+    return y < x ? y : x;
+}
+
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v)
+{
+    v = lane_sum<1>(v);
+    v = lane_sum<2>(v);
+    v = lane_sum<4>(v);
+    v = lane_sum<8>(v);
+    v = lane_sum<16>(v);
+    return lane_sum<32>(v);
+}
+
+template <typename T>
+__device__ __forceinline__ T wave_min(T v)
+{
+    v = lane_min<1>(v);
+    v = lane_min<2>(v);
+    v = lane_min<4>(v);
+    v = lane_min<8>(v);
+    v = lane_min<16>(v);
+    return lane_min<32>(v);
+}
+
+__device__ __forceinline__ int32_t wave_sum_i32(int32_t v) { return wave_sum(v); }
+__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) { return wave_sum(v); }
 __device__ __forceinline__ int64_t min_i64(int64_t a, int64_t b) { return b < a ? b : a; }
-
-__device__ __forceinline__ int64_t wave_min_i64(int64_t v)
-{
-    v = min_i64(v, lane_xor<1>(v));
-    v = min_i64(v, lane_xor<2>(v));
-    v = min_i64(v, lane_xor<4>(v));
-    v = min_i64(v, lane_xor<8>(v));
-    v = min_i64(v, lane_xor<16>(v));
-    v = min_i64(v, lane_xor<32>(v));
-    return v;
-}
-
-__device__ __forceinline__ int32_t wave_max_i32(int32_t v)
-{
-    int32_t u;
-    u = lane_xor<1>(v);  v = u > v ? u : v;
-    u = lane_xor<2>(v);  v = u > v ? u : v;
-    u = lane_xor<4>(v);  v = u > v ? u : v;
-    u = lane_xor<8>(v);  v = u > v ? u : v;
-    u = lane_xor<16>(v); v = u > v ? u : v;
-    u = lane_xor<32>(v); v = u > v ? u : v;
-    return v;
-}
+__device__ __forceinline__ int64_t wave_min_i64(int64_t v) { return wave_min(v); }
+__device__ __forceinline__ int32_t wave_max_i32(int32_t v) { return ~wave_min(~v); }
 
 // Inclusive prefix sum over the 64 lanes of a wave, by DPP lane moves:
 // within each 16-lane row every lane adds the lanes 1, 2, 4 and 8 below it
@@ -445,13 +461,7 @@ __device__ inline void split_for_sizes_wave(const SweepArgs& a, int32_t na, int3
     int64_t jc;
     float t = split_cost(a, na, L, split_items(a, lane % kSplitCands), &jc);
     if (lane >= 7 * kSplitCands || !split_lanes_ok(a, na, L, *L_io)) t = 3.0e38f;
-    float m = t, u;
-    u = lane_partner<1>(m);  m = u < m ? u : m;
-    u = lane_partner<2>(m);  m = u < m ? u : m;
-    u = lane_partner<4>(m);  m = u < m ? u : m;
-    u = lane_partner<8>(m);  m = u < m ? u : m;
-    u = lane_partner<16>(m); m = u < m ? u : m;
-    u = lane_partner<32>(m); m = u < m ? u : m;
+    const float m = wave_min(t);
     const int w = __builtin_ctzll(__ballot(t == m) | (1ull << 63));
     const int lo = __builtin_amdgcn_readlane((int)jc, w);
     const int hi = __builtin_amdgcn_readlane((int)(jc >> 32), w);
@@ -733,9 +743,9 @@ template <int O>
 __device__ __forceinline__ void wave_sum_step(double* out, float& ea, float& ej)
 {
 #pragma unroll
-    for (int q = 0; q < kRows - 1; ++q) out[q] += lane_partner<O>(out[q]);
-    ea += lane_partner<O>(ea);
-    ej += lane_partner<O>(ej);
+    for (int q = 0; q < kRows - 1; ++q) out[q] = lane_sum<O>(out[q]);
+    ea = lane_sum<O>(ea);
+    ej = lane_sum<O>(ej);
 }
 
 // The same sum by a whole wave (for many chunks): lane l adds chunks

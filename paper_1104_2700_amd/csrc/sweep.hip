@@ -39,6 +39,7 @@
 //           acceleration and potential summed as in MIXED, the jerk kept in
 //           one FP32 running sum per lane for the whole j-range.
 #include "hermite_internal.h"
+#include "pair.h"
 #include "plan.h"
 
 #include <algorithm>
@@ -57,17 +58,6 @@ constexpr int kMixedKLong = 32;
 #define HM_MIXED_NR 0
 #endif
 
-__device__ __forceinline__ double rsqrt_f64(double s)
-{
-    // y0 from the hardware; with e = 1 - s y0^2,
-    // 1/sqrt(s) = y0 (1 - e)^{-1/2} = y0 (1 + e/2 + 3 e^2 / 8 + ...).
-    const double y = __builtin_amdgcn_rsq(s);
-    const double h = s * y;
-    const double e = fma(-h, y, 1.0);
-    const double p = fma(e, 0.375, 0.5);
-    return fma(y * e, p, y);
-}
-
 __global__ void __launch_bounds__(kWG) plan_kernel(SweepArgs a)
 {
     plan_body(a, a.n_act_dev ? *a.n_act_dev : a.n_act_max);
@@ -76,26 +66,6 @@ __global__ void __launch_bounds__(kWG) plan_kernel(SweepArgs a)
 // ------------------------------------------------------------------------
 // Accumulators and pair interactions
 // ------------------------------------------------------------------------
-struct I64 {   // i-particle in FP64
-    double x, y, z, vx, vy, vz;
-};
-
-struct SumD {  // FP64 sums: acc, jerk, sum of m/r; FP32 error estimates
-    double ax, ay, az, jx, jy, jz, pp;
-    float ea, ej;  // sums over FP32 runs of |run sum|^2 (acc, jerk)
-    __device__ __forceinline__ void zero()
-    {
-        ax = ay = az = jx = jy = jz = pp = 0.0;
-        ea = ej = 0.0f;
-    }
-    __device__ __forceinline__ void add(const SumD& o)
-    {
-        ax += o.ax; ay += o.ay; az += o.az;
-        jx += o.jx; jy += o.jy; jz += o.jz;
-        pp += o.pp;
-    }
-};
-
 struct SumF {  // FP32 run sums
     float ax, ay, az, jx, jy, jz, pp;
     __device__ __forceinline__ void zero()
@@ -136,33 +106,6 @@ struct Sum2F {
         ea = ej = 0.0f;
     }
 };
-
-// One FP64 pair term: with b3 = 3 (r.v) / s,
-//   acc += m/s^{3/2} r,  jerk += m/s^{3/2} (v - b3 r),  pp += m/s^{1/2}.
-template <bool MASK>
-__device__ __forceinline__ void pair_f64(const I64& I, double eps2, double xj,
-                                         double yj, double zj, double vxj,
-                                         double vyj, double vzj, double mj,
-                                         bool self, SumD& S)
-{
-    const double dx = xj - I.x, dy = yj - I.y, dz = zj - I.z;
-    const double dvx = vxj - I.vx, dvy = vyj - I.vy, dvz = vzj - I.vz;
-    const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
-    double ri = rsqrt_f64(r2);
-    if (MASK) ri = self ? 0.0 : ri;
-    const double mr = mj * ri;
-    const double ri2 = ri * ri;
-    const double mr3 = mr * ri2;
-    const double rv = fma(dx, dvx, fma(dy, dvy, dz * dvz));
-    const double b3 = (rv * ri2) * 3.0;
-    S.pp += mr;
-    S.ax = fma(mr3, dx, S.ax);
-    S.ay = fma(mr3, dy, S.ay);
-    S.az = fma(mr3, dz, S.az);
-    S.jx = fma(mr3, fma(-b3, dx, dvx), S.jx);
-    S.jy = fma(mr3, fma(-b3, dy, dvy), S.jy);
-    S.jz = fma(mr3, fma(-b3, dz, dvz), S.jz);
-}
 
 template <bool MASK>
 __device__ __forceinline__ void pot_f64(const I64& I, double eps2, double xj,
@@ -726,7 +669,7 @@ __device__ __forceinline__ void tile_sp(const TileSP& T, int cnt, int sub, int L
         });
 }
 
-// One step of the L lanes' butterfly (see lane_partner) for all seven rows,
+// One step of the L lanes' butterfly (see lane_both) for all seven rows,
 // both error estimates and, in the paper-faithful mode, the FP32 jerk sums
 // of every particle of the lane.
 template <int O, int IPL, bool SP>
@@ -736,12 +679,12 @@ __device__ __forceinline__ void lanes_sum_step(double (&out)[IPL][kRows], float 
 #pragma unroll
     for (int q = 0; q < IPL; ++q) {
 #pragma unroll
-        for (int r = 0; r < 7; ++r) out[q][r] += lane_partner<O>(out[q][r]);
-        ea[q] += lane_partner<O>(ea[q]);
-        ej[q] += lane_partner<O>(ej[q]);
+        for (int r = 0; r < 7; ++r) out[q][r] = lane_sum<O>(out[q][r]);
+        ea[q] = lane_sum<O>(ea[q]);
+        ej[q] = lane_sum<O>(ej[q]);
         if constexpr (SP) {
 #pragma unroll
-            for (int r = 0; r < 3; ++r) fj[q][r] += lane_partner<O>(fj[q][r]);
+            for (int r = 0; r < 3; ++r) fj[q][r] = lane_sum<O>(fj[q][r]);
         }
     }
 }
