@@ -16,7 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhermite.so")
-SOURCES = ["hermite_lib.hip", "sweep.hip", "pairs.hip", "integrate.hip"]
+SOURCES = ["hermite_lib.hip", "sweep.hip", "pairs.hip", "integrate.hip",
+           "smallrun.hip"]
 ARCH = os.environ.get("HERMITE_OFFLOAD_ARCH", "gfx950")
 
 

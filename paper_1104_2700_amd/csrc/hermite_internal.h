@@ -311,6 +311,57 @@ hipError_t launch_level_build(const LevelArgs& L, hipStream_t st);
 hipError_t launch_level_select(const LevelArgs& L, const SweepArgs& sa, hipStream_t st);
 hipError_t launch_correct_reduce(const CorrectArgs& c, const SweepArgs& sa, hipStream_t st);
 
+// Whole block steps of one small system in one launch (smallrun.hip).
+constexpr int kSmallRunMax = 1536;       // particles
+constexpr int kSmallRunGrid = 64;        // workgroups
+
+// What a launch did; in pinned host memory, written by the kernel's end.
+struct SmallRunStatus {
+    int64_t launch;      // the launch that wrote it
+    int64_t done;        // 1: committed; 0: given up (a workgroup waited too
+                         // long for another), the state is as before
+    int64_t steps;       // block steps done (with active particles)
+    int64_t interactions;
+    int64_t T;           // the last block time selected (> T_end: the end)
+    int64_t na;          // its active particles (0 past T_end)
+    int64_t bad;         // a non-finite value was found
+};
+
+struct SmallRunArgs {
+    int64_t n;
+    int tick_bits;
+    double* x;
+    double* v;
+    double* a;
+    double* j;
+    double* pot;
+    const double* m;
+    int64_t* t;
+    int64_t* dt;
+    double eps2;
+    double eta;
+    int form, k_min, k_max;
+    int64_t T_end;
+    int64_t steps;            // block steps to do at most
+    int32_t check_every;      // finiteness check after every so many
+    double* xbuf;             // [2][n][kSmallRunRec] records of a step's active particles
+    int64_t* flags;           // [kSmallRunGrid] on lines of their own, then the verdict
+    int64_t epoch;            // flags count from here (never reused)
+    int64_t launch;           // verdicts are 2 launch (commit) or 2 launch + 1 (given up)
+    int64_t patience;         // wall clock ticks a workgroup waits for the others
+    int64_t* counters;
+    int32_t* na_out;
+    int64_t* T_out;
+    SmallRunStatus* status;   // pinned host memory
+};
+constexpr int kSmallRunRec = 13;      // x, v, a, j and the new step
+constexpr int kSmallRunLine = 16;     // int64 per flag (a 128-byte line)
+
+// True when a run of this system may go by launch_small_run: the plan of
+// every block has 64 lanes a particle and chunks of one tile.
+bool small_run_fits(const SweepArgs& a);
+hipError_t launch_small_run(const SmallRunArgs& r, hipStream_t st);
+
 hipError_t launch_init_dt(int64_t n, int tick_bits, const double* a,
                           const double* j, int64_t* t, int64_t* dt,
                           double eta, int form, double eta_init, int k_min, int k_max,

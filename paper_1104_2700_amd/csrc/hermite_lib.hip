@@ -86,11 +86,20 @@ struct hermite_ctx {
     // step-size order of a run (hermite_run)
     Buf lvl_perm, lvl_tmp, lvl_cnt, lvl_cursor, lvl_misc, lvl_na, lvl_bits, lvl_lv, lvl_cst;
     Buf lvl_ccnt, lvl_ccum, lvl_cna;   // ensembles: per-cluster orders
+    // small systems' runs: records and flags, the status in pinned host
+    // memory, and the numbers their flags and verdicts have reached
+    Buf small_x, small_flags;
+    SmallRunStatus* small_status = nullptr;
+    int64_t small_epoch = 0, small_launch = 0;
+    // how long their workgroups wait for each other: two seconds of the
+    // 100 MHz wall clock
+    int64_t small_patience = 200000000;
     std::vector<GraphEntry> graphs;
     // grid of the fused select + sweep for the last shape it was sized for
     struct {
         int64_t n = -1, cap = 0;
         int32_t lanes = 0, min_j = 0, ipl = 0, grid = 0;
+        bool small_run = false;
     } fused;
 };
 
@@ -600,6 +609,25 @@ int level_init(hermite_ctx* c, const hermite_state* s, const hermite_clusters* c
     return HERMITE_OK;
 }
 
+// Sizes the fused select + sweep for a's system (once per shape): the grid
+// that any active count fills at most, returned, and whether whole runs may
+// go by launch_small_run.
+int32_t size_fused(hermite_ctx* c, const SweepArgs& a)
+{
+    auto& f = c->fused;
+    if (f.n != a.n || f.cap != a.partial_cap || f.lanes != a.target_lanes ||
+        f.min_j != a.min_j_per_lane || f.ipl != a.ipl) {
+        f.n = a.n;
+        f.cap = a.partial_cap;
+        f.lanes = a.target_lanes;
+        f.min_j = a.min_j_per_lane;
+        f.ipl = a.ipl;
+        f.grid = max_plan_items(a);
+        f.small_run = small_run_fits(a);
+    }
+    return f.grid;
+}
+
 // One block step on stream st using the context's step scratch: selection
 // with the sweep plan (from the step-size order in a run, one kernel;
 // otherwise from t and dt: two kernels, one up to 4096 particles, or
@@ -651,17 +679,8 @@ int enqueue_step(hermite_ctx* c, const hermite_state* s, const hermite_clusters*
         a.sel_idx_out = idx;
         a.sel_na_out = na;
         a.sel_T_out = T;
-        auto& f = c->fused;
-        if (f.n != n || f.cap != a.partial_cap || f.lanes != a.target_lanes ||
-            f.min_j != a.min_j_per_lane || f.ipl != a.ipl) {
-            f.n = n;
-            f.cap = a.partial_cap;
-            f.lanes = a.target_lanes;
-            f.min_j = a.min_j_per_lane;
-            f.ipl = a.ipl;
-            f.grid = max_plan_items(a);
-        }
-        HIP_OK(launch_select_sweep(a, precision, tu.variant, std::min(grid, f.grid), st));
+        HIP_OK(launch_select_sweep(a, precision, tu.variant, std::min(grid, size_fused(c, a)),
+                                   st));
     } else {
         HIP_OK(launch_step_select(n, s->t, s->dt, T_end, idx, na, T, (int64_t*)c->sel_min.p,
                                   (int32_t*)c->sel_cnt.p, counters, (uint32_t*)c->ticket.p, a,
@@ -886,7 +905,7 @@ int hermite_destroy(hermite_ctx* c)
                    &c->partial, &c->ref_pos, &c->ref_idx, &c->ref_p, &c->ref_tmp,
                    &c->ref_ucnt, &c->ref_ccnt,
                    &c->rplan, &c->ract_start, &c->ract_cnt, &c->rchunks, &c->ritem_off,
-                   &c->pair,
+                   &c->pair, &c->small_x, &c->small_flags,
                    &c->sel_min, &c->sel_cnt, &c->step_idx, &c->step_na,
                    &c->step_T, &c->step_out, &c->step_acl, &c->phi, &c->counters,
                    &c->ticket, &c->flag, &c->lvl_perm, &c->lvl_tmp, &c->lvl_cnt,
@@ -894,6 +913,7 @@ int hermite_destroy(hermite_ctx* c)
                    &c->lvl_ccnt, &c->lvl_ccum, &c->lvl_cna, &c->lvl_bits};
     for (Buf* b : bufs)
         if (b->p) (void)hipFree(b->p);
+    if (c->small_status) (void)hipHostFree(c->small_status);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     delete c;
     return HERMITE_OK;
@@ -1279,6 +1299,103 @@ int hermite_block_histogram(hermite_ctx* c, int64_t out[33], void* stream)
     return HERMITE_OK;
 }
 
+// Not part of the ABI: sets how long (wall clock ticks) the workgroups of a
+// small system's run wait for each other before the launch is given up
+// (negative: it gives up at once).  For the tests of what follows then.
+int hermite_small_run_patience(hermite_ctx* c, int64_t ticks)
+{
+    if (!c) return fail(HERMITE_EINVAL, "null context");
+    c->small_patience = ticks;
+    return HERMITE_OK;
+}
+
+// The run of one small system in FP64 by launches of many steps each
+// (launch_small_run).  *launched counts the steps asked for; *ended is set
+// when the run is over (T_end, max_steps) and cleared when the rest is to be
+// taken step by step (not such a system, or a launch was given up).
+static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int precision,
+                     const hermite_dt_params* p, int64_t T_end, int32_t sync_every,
+                     int64_t max_steps, hipStream_t st, int64_t* launched, int64_t* steps,
+                     int64_t* interactions, int32_t* done, bool* ended)
+{
+    *ended = false;
+    const int64_t n = s->n;
+    const bool fp64 = precision == HERMITE_FP64 ||
+                      ((precision == HERMITE_MIXED || precision == HERMITE_MIXED_2F) &&
+                       n < c->fp64_below[precision]);
+    if (!fp64 || n > kSmallRunMax) return HERMITE_OK;
+    CHECK(ensure_step_scratch(c, n));
+    const hermite_tuning& tu = c->tuning[precision];
+    double* out = (double*)c->step_out.p;
+    SweepArgs a;
+    CHECK(prepare_sweep(c, s, nullptr, s->xp, s->vp, (int32_t*)c->step_idx.p,
+                        (int32_t*)c->step_na.p, (int32_t)n, eps2, precision, tu, out,
+                        out + 3 * n, out + 6 * n, &a));
+    a.ipl = (tu.variant & 1) ? 2 : 1;
+    (void)size_fused(c, a);
+    if (!c->fused.small_run) return HERMITE_OK;
+    CHECK(ensure(c, c->small_x, sizeof(double) * 2 * kSmallRunRec * kSmallRunMax));
+    if (!c->small_flags.p) {
+        const size_t bytes = sizeof(int64_t) * kSmallRunLine * (kSmallRunGrid + 1);
+        CHECK(ensure(c, c->small_flags, bytes));
+        HIP_OK(hipMemsetAsync(c->small_flags.p, 0, bytes, st));
+    }
+    if (!c->small_status)
+        HIP_OK(hipHostMalloc((void**)&c->small_status, sizeof(SmallRunStatus), hipHostMallocDefault));
+    SmallRunArgs r;
+    std::memset(&r, 0, sizeof r);
+    r.n = n;
+    r.tick_bits = s->tick_bits;
+    r.x = s->x;
+    r.v = s->v;
+    r.a = s->a;
+    r.j = s->j;
+    r.pot = s->pot;
+    r.m = s->m;
+    r.t = s->t;
+    r.dt = s->dt;
+    r.eps2 = eps2;
+    r.eta = p->eta;
+    r.form = p->form;
+    r.k_min = p->k_min;
+    r.k_max = p->k_max;
+    r.T_end = T_end;
+    r.check_every = sync_every;
+    r.xbuf = (double*)c->small_x.p;
+    r.flags = (int64_t*)c->small_flags.p;
+    r.patience = c->small_patience;
+    r.counters = (int64_t*)c->counters.p;
+    r.na_out = (int32_t*)c->step_na.p;
+    r.T_out = (int64_t*)c->step_T.p;
+    r.status = c->small_status;
+    // steps of a launch: the host's checks fall on its ends
+    constexpr int64_t kLaunchSteps = 65536;
+    const int64_t chunk = std::max<int64_t>(kLaunchSteps / sync_every, 1) * sync_every;
+    for (;;) {
+        r.steps = max_steps > 0 ? std::min(chunk, max_steps - *launched) : chunk;
+        r.epoch = c->small_epoch;
+        r.launch = ++c->small_launch;
+        c->small_epoch += r.steps + 2;
+        HIP_OK(launch_small_run(r, st));
+        HIP_OK(hipStreamSynchronize(st));
+        const SmallRunStatus h = *c->small_status;
+        if (h.launch != r.launch) return fail(HERMITE_EHIP, "small-system run: no status");
+        if (!h.done) return HERMITE_OK;
+        *launched += r.steps;
+        *steps += h.steps;
+        *interactions += h.interactions;
+        if (h.bad)
+            return fail(HERMITE_ENONFINITE,
+                        "non-finite state after block time %lld ticks (e.g. coincident "
+                        "particles with zero softening)", (long long)h.T);
+        if (h.na == 0 || h.T >= T_end) *done = 1;
+        if (*done || (max_steps > 0 && *launched >= max_steps)) {
+            *ended = true;
+            return HERMITE_OK;
+        }
+    }
+}
+
 int hermite_run(hermite_ctx* c, const hermite_state* s, const hermite_clusters* cl,
                 double eps2, int precision, const hermite_dt_params* p, int64_t T_end,
                 int use_graph, int32_t sync_every, int64_t max_steps, int64_t* steps_out,
@@ -1292,7 +1409,22 @@ int hermite_run(hermite_ctx* c, const hermite_state* s, const hermite_clusters* 
     if (T_end < 0 || T_end % dtmax != 0)
         return fail(HERMITE_EINVAL, "T_end must be a non-negative multiple of 2^(tick_bits-k_min)");
     hipStream_t st = (hipStream_t)stream;
-    int64_t c0[5], c1[5];
+    int64_t launched = 0, small_steps = 0, small_inter = 0;
+    int32_t done = 0;
+    if (!cl && use_graph && s->n <= kSmallRunMax) {
+        CHECK(check_precision(precision));
+        CHECK(check_eps2(eps2));
+        bool ended = false;
+        CHECK(small_run(c, s, eps2, precision, p, T_end, sync_every, max_steps, st, &launched,
+                        &small_steps, &small_inter, &done, &ended));
+        if (ended) {
+            if (steps_out) *steps_out = small_steps;
+            if (interactions_out) *interactions_out = small_inter;
+            if (done_out) *done_out = done;
+            return HERMITE_OK;
+        }
+    }
+    int64_t c0[6], c1[6];
     CHECK(hermite_counters(c, c0, stream));
     // Select from the step-size order unless the sweep selects itself (one
     // small system) or the clusters do not fit the selection's LDS tables.
@@ -1302,8 +1434,6 @@ int hermite_run(hermite_ctx* c, const hermite_state* s, const hermite_clusters* 
         CHECK(ensure_step_scratch(c, s->n));
         CHECK(level_init(c, s, cl, p, st, &level));
     }
-    int64_t launched = 0;
-    int32_t done = 0;
     for (;;) {
         int batch = sync_every;
         if (max_steps > 0 && launched + batch > max_steps) batch = (int)(max_steps - launched);
@@ -1339,8 +1469,8 @@ int hermite_run(hermite_ctx* c, const hermite_state* s, const hermite_clusters* 
         if (max_steps > 0 && launched >= max_steps) break;
     }
     CHECK(hermite_counters(c, c1, stream));
-    if (steps_out) *steps_out = c1[0] - c0[0];
-    if (interactions_out) *interactions_out = c1[1] - c0[1];
+    if (steps_out) *steps_out = small_steps + c1[0] - c0[0];
+    if (interactions_out) *interactions_out = small_inter + c1[1] - c0[1];
     if (done_out) *done_out = done;
     return HERMITE_OK;
 }
