@@ -287,7 +287,10 @@ int hermite_step(hermite_ctx* ctx, const hermite_state* s,
  * a non-finite state ends the call with HERMITE_ENONFINITE.  With
  * use_graph != 0, runs of 8 consecutive steps are captured as one graph
  * (steps past T_end are no-ops), which removes the gap between graph
- * launches that dominates small systems.
+ * launches that dominates small systems; one system of n <= 16384 swept in
+ * FP64 (with the default tuning) takes many steps in one launch instead,
+ * whose workgroups wait for each other on the device (bounded: a launch that
+ * cannot get the device's compute units is taken step by step).
  *
  * Block selection in a run (Section 2's block scheme): at the start of the
  * call the particles are ordered by step size (one pass over t and dt,

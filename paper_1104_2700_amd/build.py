@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhermite.so")
 SOURCES = ["hermite_lib.hip", "sweep.hip", "pairs.hip", "integrate.hip",
-           "smallrun.hip"]
+           "smallrun.hip", "midrun.hip"]
 ARCH = os.environ.get("HERMITE_OFFLOAD_ARCH", "gfx950")
 
 

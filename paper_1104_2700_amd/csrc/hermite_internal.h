@@ -77,6 +77,8 @@ struct SweepArgs {
     int32_t auto_split;
     int32_t n_cu;
     int32_t split_fp64;        // the sweep is FP64
+    int32_t split_tiles;       // nonzero: chunks of a power of two of tiles, this
+                               // many at most (where the partial sums have room)
     int32_t split_res;
     float split_cyc;
     int32_t one_chunk;         // nonzero: no j-split across work items (the
@@ -325,6 +327,7 @@ struct SmallRunStatus {
     int64_t T;           // the last block time selected (> T_end: the end)
     int64_t na;          // its active particles (0 past T_end)
     int64_t bad;         // a non-finite value was found
+    int64_t handoff;     // the next block is not one for these launches
 };
 
 struct SmallRunArgs {
@@ -361,6 +364,44 @@ constexpr int kSmallRunLine = 16;     // int64 per flag (a 128-byte line)
 // every block has 64 lanes a particle and chunks of one tile.
 bool small_run_fits(const SweepArgs& a);
 hipError_t launch_small_run(const SmallRunArgs& r, hipStream_t st);
+
+// The same for one system beyond kSmallRunMax particles (midrun.hip).
+constexpr int kMidThreads = 512;      // a workgroup's
+constexpr int kMidSlice = 1024;       // particles of a workgroup
+constexpr int kMidMaxSlices = 16;
+constexpr int kMidRunMax = kMidMaxSlices * kMidSlice;
+constexpr int kMidRowSlots = 64;      // due particles a slice sends to its own row
+constexpr int kMidLine = 16;          // words of a record (a 128-byte line)
+
+// Header words of a grid, those of workgroups b, b + 8, ... on lines of their own.
+__host__ __device__ inline int mid_header_words(int grid)
+{
+    return 8 * (((grid + 7) / 8 + kMidLine - 1) / kMidLine * kMidLine);
+}
+
+struct MidRunShape {
+    int slices, rows;                 // rows 0: the device is too small
+    int64_t partial_lines;
+};
+
+// Exchange buffers (words, zeroed before their first use: no tag is 0).
+struct MidRunArgs {
+    int slices, rows;
+    uint32_t rows_inverse;    // ceil(2^32 / rows)
+    int model;                // plans follow split_for_sizes from kSplitMinInter on
+    int64_t partial_lines;
+    uint64_t* header;         // [3][3][mid_header_words]: the last for the end
+    uint64_t* row_due;        // [2][rows slices][kMidRowSlots] lines
+    uint64_t* all_due;        // [2][slices slice] lines
+    uint64_t* partial;        // [rows slices][partial_lines] lines
+    uint64_t* corrected;      // [slices slice] pairs of lines
+    uint8_t* plans;           // [n + 1]
+    int64_t* verdict;
+};
+
+MidRunShape mid_run_shape(int64_t n, int n_cu);
+hipError_t launch_mid_run(const SmallRunArgs& r, const MidRunArgs& e, const SweepArgs& sa,
+                          hipStream_t st);
 
 hipError_t launch_init_dt(int64_t n, int tick_bits, const double* a,
                           const double* j, int64_t* t, int64_t* dt,

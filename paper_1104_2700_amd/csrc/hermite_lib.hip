@@ -11,8 +11,10 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
+#include <functional>
 #include <map>
 #include <mutex>
+#include <shared_mutex>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -91,6 +93,9 @@ struct hermite_ctx {
     Buf small_x, small_flags;
     SmallRunStatus* small_status = nullptr;
     int64_t small_epoch = 0, small_launch = 0;
+    Buf mid_x, mid_flag;   // the same for runs by launch_mid_run
+    int64_t mid_epoch = 1;
+    int64_t runs_on_chip = 0, runs_given_up = 0, runs_handed_off = 0;
     // how long their workgroups wait for each other: two seconds of the
     // 100 MHz wall clock
     int64_t small_patience = 200000000;
@@ -628,6 +633,14 @@ int32_t size_fused(hermite_ctx* c, const SweepArgs& a)
     return f.grid;
 }
 
+// Block steps: chunks that tile the slices of launch_mid_run, so that runs
+// and single steps add alike.
+void tile_slices(SweepArgs* a)
+{
+    if (a->auto_split && a->split_fp64 && a->n > kSmallRunMax && a->n <= kMidRunMax)
+        a->split_tiles = kMidSlice / kTJ;
+}
+
 // One block step on stream st using the context's step scratch: selection
 // with the sweep plan (from the step-size order in a run, one kernel;
 // otherwise from t and dt: two kernels, one up to 4096 particles, or
@@ -651,6 +664,7 @@ int enqueue_step(hermite_ctx* c, const hermite_state* s, const hermite_clusters*
     CHECK(prepare_sweep(c, s, cl, s->xp, s->vp, aidx, na, (int32_t)n, eps2, precision, tu, out,
                         out + 3 * n, out + 6 * n, &a));
     a.ipl = (tu.variant & 1) ? 2 : 1;
+    if (!cl) tile_slices(&a);
     // a block the plan puts in FP64 takes the refine sweep's launch (over
     // the whole block) and the corrector's reduce
     a.defer_fp64 = a.refine;
@@ -905,7 +919,7 @@ int hermite_destroy(hermite_ctx* c)
                    &c->partial, &c->ref_pos, &c->ref_idx, &c->ref_p, &c->ref_tmp,
                    &c->ref_ucnt, &c->ref_ccnt,
                    &c->rplan, &c->ract_start, &c->ract_cnt, &c->rchunks, &c->ritem_off,
-                   &c->pair, &c->small_x, &c->small_flags,
+                   &c->pair, &c->small_x, &c->small_flags, &c->mid_x, &c->mid_flag,
                    &c->sel_min, &c->sel_cnt, &c->step_idx, &c->step_na,
                    &c->step_T, &c->step_out, &c->step_acl, &c->phi, &c->counters,
                    &c->ticket, &c->flag, &c->lvl_perm, &c->lvl_tmp, &c->lvl_cnt,
@@ -1309,10 +1323,67 @@ int hermite_small_run_patience(hermite_ctx* c, int64_t ticks)
     return HERMITE_OK;
 }
 
-// The run of one small system in FP64 by launches of many steps each
-// (launch_small_run).  *launched counts the steps asked for; *ended is set
-// when the run is over (T_end, max_steps) and cleared when the rest is to be
-// taken step by step (not such a system, or a launch was given up).
+// Not part of the ABI: launches of many block steps so far, how many of them
+// were given up, and how many ended before a block they cannot take.
+int hermite_small_run_launches(hermite_ctx* c, int64_t out[3])
+{
+    if (!c) return fail(HERMITE_EINVAL, "null context");
+    out[0] = c->runs_on_chip;
+    out[1] = c->runs_given_up;
+    out[2] = c->runs_handed_off;
+    return HERMITE_OK;
+}
+
+// Who may hold a device's compute units for many steps: up to four launches
+// of launch_small_run (64 workgroups each, and a process has four hardware
+// queues), or one of launch_mid_run (a workgroup a unit).  More would wait
+// for each other's places; who does not get in takes single steps.
+static std::shared_mutex g_chip[64];
+
+// Launches r (r.steps and the verdict's numbers set here) until the run is
+// over or is to be taken step by step.
+static int run_launches(hermite_ctx* c, SmallRunArgs& r, int64_t launch_steps, int64_t* epoch,
+                        int64_t max_steps, hipStream_t st, int64_t* launched, int64_t* steps,
+                        int64_t* interactions, int32_t* done, bool* ended,
+                        const std::function<int(bool*)>& launch)
+{
+    // steps of a launch: the host's checks fall on its ends
+    const int64_t chunk = std::max<int64_t>(launch_steps / r.check_every, 1) * r.check_every;
+    for (;;) {
+        r.steps = max_steps > 0 ? std::min(chunk, max_steps - *launched) : chunk;
+        r.epoch = *epoch;
+        r.launch = ++c->small_launch;
+        *epoch += r.steps + 2;
+        bool in = false;
+        CHECK(launch(&in));
+        if (!in) return HERMITE_OK;
+        const SmallRunStatus h = *c->small_status;
+        if (h.launch != r.launch) return fail(HERMITE_EHIP, "run of many steps: no status");
+        ++c->runs_on_chip;
+        if (!h.done) ++c->runs_given_up;
+        else if (h.handoff) ++c->runs_handed_off;
+        if (!h.done) return HERMITE_OK;
+        *launched += h.handoff ? h.steps : r.steps;
+        *steps += h.steps;
+        *interactions += h.interactions;
+        if (h.bad)
+            return fail(HERMITE_ENONFINITE,
+                        "non-finite state after block time %lld ticks (e.g. coincident "
+                        "particles with zero softening)", (long long)h.T);
+        if (h.handoff) return HERMITE_OK;
+        if (h.na == 0 || h.T >= r.T_end) *done = 1;
+        if (*done || (max_steps > 0 && *launched >= max_steps)) {
+            *ended = true;
+            return HERMITE_OK;
+        }
+    }
+}
+
+// The run of one system in FP64 by launches of many steps each
+// (launch_small_run, launch_mid_run).  *launched counts the steps asked for;
+// *ended is set when the run is over (T_end, max_steps) and cleared when the
+// rest is to be taken step by step (not such a system, or a launch was given
+// up).
 static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int precision,
                      const hermite_dt_params* p, int64_t T_end, int32_t sync_every,
                      int64_t max_steps, hipStream_t st, int64_t* launched, int64_t* steps,
@@ -1323,7 +1394,7 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
     const bool fp64 = precision == HERMITE_FP64 ||
                       ((precision == HERMITE_MIXED || precision == HERMITE_MIXED_2F) &&
                        n < c->fp64_below[precision]);
-    if (!fp64 || n > kSmallRunMax) return HERMITE_OK;
+    if (!fp64 || n > kMidRunMax || c->device >= 64) return HERMITE_OK;
     CHECK(ensure_step_scratch(c, n));
     const hermite_tuning& tu = c->tuning[precision];
     double* out = (double*)c->step_out.p;
@@ -1332,13 +1403,15 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
                         (int32_t*)c->step_na.p, (int32_t)n, eps2, precision, tu, out,
                         out + 3 * n, out + 6 * n, &a));
     a.ipl = (tu.variant & 1) ? 2 : 1;
-    (void)size_fused(c, a);
-    if (!c->fused.small_run) return HERMITE_OK;
-    CHECK(ensure(c, c->small_x, sizeof(double) * 2 * kSmallRunRec * kSmallRunMax));
-    if (!c->small_flags.p) {
-        const size_t bytes = sizeof(int64_t) * kSmallRunLine * (kSmallRunGrid + 1);
-        CHECK(ensure(c, c->small_flags, bytes));
-        HIP_OK(hipMemsetAsync(c->small_flags.p, 0, bytes, st));
+    tile_slices(&a);
+    const bool mid = n > kSmallRunMax;
+    MidRunShape shape = {};
+    if (mid) {
+        shape = mid_run_shape(n, c->n_cu);
+        if (!a.auto_split || shape.rows < 2) return HERMITE_OK;
+    } else {
+        (void)size_fused(c, a);
+        if (!c->fused.small_run) return HERMITE_OK;
     }
     if (!c->small_status)
         HIP_OK(hipHostMalloc((void**)&c->small_status, sizeof(SmallRunStatus), hipHostMallocDefault));
@@ -1361,39 +1434,71 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
     r.k_max = p->k_max;
     r.T_end = T_end;
     r.check_every = sync_every;
-    r.xbuf = (double*)c->small_x.p;
-    r.flags = (int64_t*)c->small_flags.p;
     r.patience = c->small_patience;
     r.counters = (int64_t*)c->counters.p;
     r.na_out = (int32_t*)c->step_na.p;
     r.T_out = (int64_t*)c->step_T.p;
     r.status = c->small_status;
-    // steps of a launch: the host's checks fall on its ends
-    constexpr int64_t kLaunchSteps = 65536;
-    const int64_t chunk = std::max<int64_t>(kLaunchSteps / sync_every, 1) * sync_every;
-    for (;;) {
-        r.steps = max_steps > 0 ? std::min(chunk, max_steps - *launched) : chunk;
-        r.epoch = c->small_epoch;
-        r.launch = ++c->small_launch;
-        c->small_epoch += r.steps + 2;
-        HIP_OK(launch_small_run(r, st));
-        HIP_OK(hipStreamSynchronize(st));
-        const SmallRunStatus h = *c->small_status;
-        if (h.launch != r.launch) return fail(HERMITE_EHIP, "small-system run: no status");
-        if (!h.done) return HERMITE_OK;
-        *launched += r.steps;
-        *steps += h.steps;
-        *interactions += h.interactions;
-        if (h.bad)
-            return fail(HERMITE_ENONFINITE,
-                        "non-finite state after block time %lld ticks (e.g. coincident "
-                        "particles with zero softening)", (long long)h.T);
-        if (h.na == 0 || h.T >= T_end) *done = 1;
-        if (*done || (max_steps > 0 && *launched >= max_steps)) {
-            *ended = true;
-            return HERMITE_OK;
+    if (!mid) {
+        CHECK(ensure(c, c->small_x, sizeof(double) * 2 * kSmallRunRec * kSmallRunMax));
+        if (!c->small_flags.p) {
+            const size_t bytes = sizeof(int64_t) * kSmallRunLine * (kSmallRunGrid + 1);
+            CHECK(ensure(c, c->small_flags, bytes));
+            HIP_OK(hipMemsetAsync(c->small_flags.p, 0, bytes, st));
         }
+        r.xbuf = (double*)c->small_x.p;
+        r.flags = (int64_t*)c->small_flags.p;
+        return run_launches(c, r, 65536, &c->small_epoch, max_steps, st, launched, steps,
+                            interactions, done, ended, [&](bool* in) -> int {
+            std::shared_lock<std::shared_mutex> chip(g_chip[c->device], std::try_to_lock);
+            if (!(*in = chip.owns_lock())) return HERMITE_OK;
+            HIP_OK(launch_small_run(r, st));
+            HIP_OK(hipStreamSynchronize(st));
+            return HERMITE_OK;
+        });
     }
+    MidRunArgs e = {};
+    e.slices = shape.slices;
+    e.rows = shape.rows;
+    e.rows_inverse = (uint32_t)((((uint64_t)1 << 32) + e.rows - 1) / e.rows);
+    e.model = n > kFusedSelMax ? 1 : 0;
+    e.partial_lines = shape.partial_lines;
+    const size_t grid = (size_t)e.slices * e.rows, line = kMidLine * sizeof(uint64_t);
+    const size_t head = sizeof(uint64_t) * 9 * mid_header_words((int)grid);
+    const size_t row = 2 * grid * kMidRowSlots * line;
+    const size_t all = 2 * (size_t)e.slices * kMidSlice * line;
+    const size_t part = grid * (size_t)e.partial_lines * line;
+    const size_t bytes = head + row + all + part + all + (size_t)n + 1;
+    const bool grown = c->mid_x.bytes < bytes || !c->mid_flag.p;
+    // (without the memory for it: single steps)
+    if (ensure(c, c->mid_x, bytes) != HERMITE_OK) return HERMITE_OK;
+    CHECK(ensure(c, c->mid_flag, sizeof(int64_t)));
+    if (grown) {
+        HIP_OK(hipMemsetAsync(c->mid_x.p, 0, c->mid_x.bytes, st));
+        HIP_OK(hipMemsetAsync(c->mid_flag.p, 0, sizeof(int64_t), st));
+    }
+    unsigned char* base = (unsigned char*)c->mid_x.p;
+    e.header = (uint64_t*)base;
+    e.row_due = (uint64_t*)(base + head);
+    e.all_due = (uint64_t*)(base + head + row);
+    e.partial = (uint64_t*)(base + head + row + all);
+    e.corrected = (uint64_t*)(base + head + row + all + part);
+    e.plans = base + head + row + all + part + all;
+    e.verdict = (int64_t*)c->mid_flag.p;
+    return run_launches(c, r, 4096, &c->mid_epoch, max_steps, st, launched, steps, interactions,
+                        done, ended, [&](bool* in) -> int {
+        std::unique_lock<std::shared_mutex> chip(g_chip[c->device], std::try_to_lock);
+        if (!(*in = chip.owns_lock())) return HERMITE_OK;
+        if ((r.epoch >> 32) != ((r.epoch + r.steps + 2) >> 32)) {
+            // the tags, 32 bits of the step's number, start over
+            r.epoch = ((r.epoch >> 32) + 1) * ((int64_t)1 << 32) + 1;
+            c->mid_epoch = r.epoch + r.steps + 2;
+            HIP_OK(hipMemsetAsync(c->mid_x.p, 0, c->mid_x.bytes, st));
+        }
+        HIP_OK(launch_mid_run(r, e, a, st));
+        HIP_OK(hipStreamSynchronize(st));
+        return HERMITE_OK;
+    });
 }
 
 int hermite_run(hermite_ctx* c, const hermite_state* s, const hermite_clusters* cl,
@@ -1411,7 +1516,7 @@ int hermite_run(hermite_ctx* c, const hermite_state* s, const hermite_clusters* 
     hipStream_t st = (hipStream_t)stream;
     int64_t launched = 0, small_steps = 0, small_inter = 0;
     int32_t done = 0;
-    if (!cl && use_graph && s->n <= kSmallRunMax) {
+    if (!cl && use_graph && s->n <= kMidRunMax) {
         CHECK(check_precision(precision));
         CHECK(check_eps2(eps2));
         bool ended = false;

@@ -112,6 +112,44 @@ __device__ __forceinline__ T wave_min(T v)
     return lane_min<32>(v);
 }
 
+// Eight values summed over L >= 8 lanes (L a power of two), the values dealt
+// out to the lanes as they are added: a lane keeps half of its values and
+// adds its partner's at each of the first three steps, so that 7 + log2(L) - 3
+// sums remain of 8 log2(L).  The sums are those of lane_sum's butterfly bit
+// for bit (which half a lane keeps follows the mirrors in its steps of 4 and
+// 8).  Every lane gets the total of its value, summed8_index.
+__device__ __forceinline__ int summed8_index()
+{
+    const int l = threadIdx.x;
+    return (((l ^ (l >> 2)) & 1) << 2) | (((l >> 1) ^ (l >> 2)) & 1) << 1 |
+           (((l >> 2) ^ (l >> 3)) & 1);
+}
+
+template <int O>
+__device__ __forceinline__ double deal_sum(double mine0, double mine1, bool second)
+{
+    const double keep = second ? mine1 : mine0, send = second ? mine0 : mine1;
+    int64_t a, b;
+    lane_both<O>((int64_t)__double_as_longlong(send), a, b);
+    return keep + __longlong_as_double((long long)b);
+}
+
+__device__ __forceinline__ double lanes_sum8(const double (&v)[8], int L)
+{
+    const int u = summed8_index();
+    const bool s0 = (u & 4) != 0, s1 = (u & 2) != 0, s2 = (u & 1) != 0;
+    double w[4], x[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = deal_sum<1>(v[k], v[k + 4], s0);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) x[k] = deal_sum<2>(w[k], w[k + 2], s1);
+    double y = deal_sum<4>(x[0], x[1], s2);
+    if (L > 8) y = lane_sum<8>(y);
+    if (L > 16) y = lane_sum<16>(y);
+    if (L > 32) y = lane_sum<32>(y);
+    return y;
+}
+
 __device__ __forceinline__ int32_t wave_sum_i32(int32_t v) { return wave_sum(v); }
 __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) { return wave_sum(v); }
 __device__ __forceinline__ int64_t min_i64(int64_t a, int64_t b) { return b < a ? b : a; }
@@ -389,7 +427,13 @@ __host__ __device__ inline float split_cost(const SweepArgs& a, int32_t na, int3
     int64_t ch = div_floor(items_want, tiles);
     if (ch > max_ch) ch = max_ch;
     if (ch < 1) ch = 1;
-    const int64_t jt = div_ceil(T, ch);
+    int64_t jt = div_ceil(T, ch);
+    if (a.split_tiles > 0) {
+        int64_t j2 = 1;
+        while (j2 < a.split_tiles && (j2 < jt || (int64_t)na * div_ceil(T, j2) > 16 * a.n))
+            j2 <<= 1;
+        if (div_ceil(T, j2) <= max_ch) jt = j2;
+    }
     ch = div_ceil(T, jt);
     *jc = jt * kTJ;
     const int64_t R = (int64_t)a.n_cu * a.split_res;
@@ -426,8 +470,9 @@ __host__ __device__ inline bool split_lanes_ok(const SweepArgs& a, int32_t na, i
     return L == 64 || (int64_t)a.ipl * (kWG / L) <= 2 * (int64_t)na;
 }
 
-// The split of least modelled time (host).
-inline void split_for_sizes(const SweepArgs& a, int32_t na, int32_t* L_io, int64_t* jc_io)
+// The split of least modelled time.
+__host__ __device__ inline void split_for_sizes(const SweepArgs& a, int32_t na, int32_t* L_io,
+                                                int64_t* jc_io)
 {
     const int32_t L_plan = *L_io;
     float best = 3.0e38f;
