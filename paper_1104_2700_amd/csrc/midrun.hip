@@ -122,7 +122,7 @@ __global__ void __launch_bounds__(kWG) mid_plan_kernel(MidRunArgs e, SweepArgs s
     int32_t L, ti;
     int64_t jc;
     plan_split(sa, na, 1, &L, &ti, &jc);
-    if (e.model && (int64_t)na * sa.n >= kSplitMinInter) split_for_sizes(sa, na, &L, &jc);
+    if (e.model && split_by_model(sa, na)) split_for_sizes(sa, na, &L, &jc);
     const bool ok = jc <= kMidSlice && kMidSlice % jc == 0 &&
                     (int64_t)((na + e.rows - 1) / e.rows) * (kMidSlice / jc) <= e.partial_lines;
     e.plans[na] = ok ? (uint8_t)((31 - __clz(L)) | (31 - __clz((int)(jc / kTJ))) << 3)

@@ -86,13 +86,16 @@ constexpr int64_t kPairFour = 20000;
 constexpr int64_t kPairWide = 45000, kPairWidePot = 24576;
 constexpr int64_t kPairMaxN = (int64_t)1 << 23;   // rows of at most 2^15 - 1 tiles
 // Ensembles whose largest cluster fits 43 blocks (16 chunks and 21 block
-// slots of partial sums), with at least 3e7 interactions (n^2 / C, a lower
-// bound: 10 clusters of 300 ... 3000, 1.4e7, take 50 us one-sided and 85 by
-// pairs; 10 of 100 ... 8000, 3.2e7, 145 and 123; 200 of 64 ... 1500, 4.1e7,
-// 239 and 141) and clusters of 256 particles on average (1500 of 30 ... 300:
-// 105 one-sided, 128 by pairs, whose blocks of 192 are half empty).
+// slots of partial sums), with at least 6e7 interactions (n^2 / C, a lower
+// bound; 4e7 from 30 clusters on, which fill the last round more evenly) and
+// clusters of 256 particles on average (1500 of 30 ... 300: 105 one-sided,
+// 128 by pairs, whose blocks of 192 are half empty).  One-sided / by pairs:
+// 20 clusters of 600 ... 2500, 3.5e7, 76 / 94 us; 7 of 600 ... 8192, 5.8e7,
+// 133 / 164; 20 of 600 ... 4000, 6.4e7, 143 / 132; 10 of 600 ... 8192, 8.4e7,
+// 241 / 171; 30 of 64 ... 5500, 4.5e7, 181 / 136.
 constexpr int64_t kPairMaxCluster = 8192, kPairMeanCluster = 256;
-constexpr double kPairEnsemble = 3.0e7;
+constexpr double kPairEnsemble = 6.0e7, kPairManyEnsemble = 4.0e7;
+constexpr int kPairMany = 30;
 constexpr int kPairClusterSlots = 16;
 
 // One particle of the sweep: coordinates (velocities), mass, sums.
@@ -426,7 +429,8 @@ bool pair_shape(int64_t n, int n_clusters, int64_t n_cmax, int n_cu, bool pot_on
     std::memset(sh, 0, sizeof *sh);
     if (n_clusters > 1) {
         const double inter = (double)n * (double)n / n_clusters;   // at least this many
-        if (n_cmax > kPairMaxCluster || n_clusters > kLdsClusters || inter < kPairEnsemble ||
+        if (n_cmax > kPairMaxCluster || n_clusters > kLdsClusters ||
+            inter < (n_clusters < kPairMany ? kPairEnsemble : kPairManyEnsemble) ||
             n / n_clusters < kPairMeanCluster)
             return false;
         sh->k = 3;

@@ -1335,8 +1335,8 @@ bool make_host_plan(SweepArgs* a, int precision, int variant, bool pot_only)
     int32_t L, ti;
     int64_t jc;
     plan_split(*a, na, 1, &L, &ti, &jc);
-    if (a->auto_split && (int64_t)na * a->n >= kSplitMinInter) {
-        if (fp64) set_split_model(a, 0, variant & 1, pot_only);
+    if (a->auto_split && fp64) set_split_model(a, 0, variant & 1, pot_only);
+    if (split_by_model(*a, na)) {
         split_for_sizes(*a, na, &L, &jc);
         ti = a->ipl * (kWG / L);
     }
