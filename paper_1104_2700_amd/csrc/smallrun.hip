@@ -63,13 +63,6 @@ struct Rec {             // an active particle of this workgroup, from its owner
     int pos;
 };
 
-template <int O>
-__device__ __forceinline__ void slot_step(double (&o)[7])
-{
-#pragma unroll
-    for (int u = 0; u < 7; ++u) o[u] = lane_sum<O>(o[u]);
-}
-
 // This wave's tile's part of the sums of one active particle.
 __device__ __forceinline__ void sweep_slot(const Rec& q, const double (&px)[kPer][3],
                                            const double (&pv)[kPer][3], const double (&m)[kPer],
@@ -84,17 +77,9 @@ __device__ __forceinline__ void sweep_slot(const Rec& q, const double (&px)[kPer
     for (int k = 0; k < kPer; ++k)
         pair_f64<true>(I, eps2, px[k][0], px[k][1], px[k][2], pv[k][0], pv[k][1], pv[k][2], m[k],
                        kTJ * wave + 64 * k + lane == i, S);
-    double o[7] = {S.ax, S.ay, S.az, S.jx, S.jy, S.jz, -S.pp};
-    slot_step<1>(o);
-    slot_step<2>(o);
-    slot_step<4>(o);
-    slot_step<8>(o);
-    slot_step<16>(o);
-    slot_step<32>(o);
-    if (lane == 0) {
-#pragma unroll
-        for (int u = 0; u < 7; ++u) part[u] = o[u];
-    }
+    const double o[8] = {S.ax, S.ay, S.az, S.jx, S.jy, S.jz, -S.pp, 0.0};
+    const double f = lanes_sum8(o, 64);
+    if (lane < 8) part[summed8_index()] = f;
 }
 
 // MAXW: waves at most (four leave a wave the registers of a whole SIMD).

@@ -689,6 +689,15 @@ __device__ __forceinline__ void lanes_sum_step(double (&out)[IPL][kRows], float 
     }
 }
 
+__device__ __forceinline__ float lanes_sum_f32(float v, int L)
+{
+    v = lane_sum<4>(lane_sum<2>(lane_sum<1>(v)));   // L >= 8
+    if (L > 8) v = lane_sum<8>(v);
+    if (L > 16) v = lane_sum<16>(v);
+    if (L > 32) v = lane_sum<32>(v);
+    return v;
+}
+
 // Final per-lane values: acc xyz, jerk xyz, pot (-sum m/r); the error
 // estimates are combined separately (they are FP32).
 __device__ __forceinline__ void finalize(const SumD& S, double out[kRows])
@@ -997,26 +1006,49 @@ sweep_kernel(SweepArgs a)
                 fj[q][2] = F[q].jz;
             }
         }
-        if (L > 1) lanes_sum_step<1, IPL, PREC == 3>(out, ea, ej, fj);
-        if (L > 2) lanes_sum_step<2, IPL, PREC == 3>(out, ea, ej, fj);
-        if (L > 4) lanes_sum_step<4, IPL, PREC == 3>(out, ea, ej, fj);
-        if (L > 8) lanes_sum_step<8, IPL, PREC == 3>(out, ea, ej, fj);
-        if (L > 16) lanes_sum_step<16, IPL, PREC == 3>(out, ea, ej, fj);
-        if (L > 32) lanes_sum_step<32, IPL, PREC == 3>(out, ea, ej, fj);
+        double* const dst0 = a.partial + (int64_t)k * kRows * na;
+        bool dealt = false;
+        if constexpr (!POT_ONLY && !SPLIT && PREC != 3) {
+            if (L >= 8) {
+                // a lane ends with one row's total: a third of the butterfly's
+                // instructions, and one store
+                dealt = true;
+                const int u = summed8_index();
 #pragma unroll
-        for (int q = 0; q < IPL; ++q) {
-            out[q][kRows - 1] = pack_est(ea[q], ej[q]);
-            if constexpr (PREC == 3) {
-#pragma unroll
-                for (int r = 0; r < 3; ++r) out[q][3 + r] += (double)fj[q][r];
+                for (int q = 0; q < IPL; ++q) {
+                    out[q][kRows - 1] = 0.0;
+                    double f = lanes_sum8(out[q], L);
+                    if constexpr (PREC != 0) {
+                        ea[q] = lanes_sum_f32(ea[q], L);
+                        ej[q] = lanes_sum_f32(ej[q], L);
+                        f = u == kRows - 1 ? pack_est(ea[q], ej[q]) : f;
+                    }
+                    if (valid[q] && sub < 8) dst0[u * (int64_t)na + pp[q]] = f;
+                }
             }
-            if (valid[q] && sub == 0) {
-                double* dst = a.partial + (int64_t)k * kRows * na + pp[q];
-                if (POT_ONLY) {
-                    dst[6 * (int64_t)na] = out[q][6];
-                } else {
+        }
+        if (!dealt) {
+            if (L > 1) lanes_sum_step<1, IPL, PREC == 3>(out, ea, ej, fj);
+            if (L > 2) lanes_sum_step<2, IPL, PREC == 3>(out, ea, ej, fj);
+            if (L > 4) lanes_sum_step<4, IPL, PREC == 3>(out, ea, ej, fj);
+            if (L > 8) lanes_sum_step<8, IPL, PREC == 3>(out, ea, ej, fj);
+            if (L > 16) lanes_sum_step<16, IPL, PREC == 3>(out, ea, ej, fj);
+            if (L > 32) lanes_sum_step<32, IPL, PREC == 3>(out, ea, ej, fj);
 #pragma unroll
-                    for (int r = 0; r < kRows; ++r) dst[r * (int64_t)na] = out[q][r];
+            for (int q = 0; q < IPL; ++q) {
+                out[q][kRows - 1] = pack_est(ea[q], ej[q]);
+                if constexpr (PREC == 3) {
+#pragma unroll
+                    for (int r = 0; r < 3; ++r) out[q][3 + r] += (double)fj[q][r];
+                }
+                if (valid[q] && sub == 0) {
+                    double* dst = dst0 + pp[q];
+                    if (POT_ONLY) {
+                        dst[6 * (int64_t)na] = out[q][6];
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < kRows; ++r) dst[r * (int64_t)na] = out[q][r];
+                    }
                 }
             }
         }
