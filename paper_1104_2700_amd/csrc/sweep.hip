@@ -1383,6 +1383,79 @@ bool make_host_plan(SweepArgs* a, int precision, int variant, bool pot_only)
     return fp64;
 }
 
+// Small blocks of one small system, FP64: a workgroup an active particle,
+// over all j, a wave a tile, so that no partial sum leaves the workgroup and
+// no second kernel adds them (it took 4.2 us and a launch of 2.5).  Bound by
+// latency (the index, the particle, its j, one wave's 256 pairs or a few times
+// that, the lanes' sums) and, from 4096 particles on, by what a compute unit
+// can read, 56 bytes a j.  The additions are those of a sweep of 64 lanes a
+// particle and one tile a chunk with its reduction, in their order.
+// Two kernels / this one, a call: 7 of 1024 10.1 / 6.5 us, 250 of 3000 12.5 /
+// 6.6, 100 of 4096 12.3 / 7.3, of 6000 10.3 / 9.0, of 8192 10.6 / 11.0, 7 of
+// 16384 10.7 / 17.8.  (16 waves: the same; 500 of 3000 9.9 against 8.8.)
+constexpr int kDirectMax = 6400;
+constexpr int64_t kDirectInter = 2000000;   // 500 of 3000 13.6 / 8.8
+constexpr int kDirectWaves = 8;
+
+__global__ void __launch_bounds__(64 * kDirectWaves) direct_kernel(SweepArgs a)
+{
+    __shared__ double s_sum[kDirectMax / kTJ][kRows];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x / 64;
+    const int n = (int)a.n, na = a.hp.n_act, ch = a.hp.s_max, p = (int)blockIdx.x;
+    count_host_plan(a);
+    const int i = a.idx ? a.idx[p] : p;
+    I64 I;
+    SumD A;
+    for (int tile = wave; tile < ch; tile += waves) {
+        double x[4][3], v[4][3], m[4];
+        bool off[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int j = kTJ * tile + 64 * k + lane, jj = j < n ? j : n - 1;
+            off[k] = j >= n || j == i;   // past the end: a masked pair too
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                x[k][d] = a.xp[d * (int64_t)n + jj];
+                v[k][d] = a.vp[d * (int64_t)n + jj];
+            }
+            m[k] = a.m[jj];
+        }
+        if (tile == wave)
+            I = I64{a.xp[i], a.xp[n + i], a.xp[2 * n + i], a.vp[i], a.vp[n + i], a.vp[2 * n + i]};
+        SumD B;
+        A.zero();
+        B.zero();
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            pair_f64<true>(I, a.eps2, x[k][0], x[k][1], x[k][2], v[k][0], v[k][1], v[k][2], m[k],
+                           off[k], B);
+        A.add(B);
+        const double o[kRows] = {A.ax, A.ay, A.az, A.jx, A.jy, A.jz, -A.pp, 0.0};
+        const double f = lanes_sum8(o, 64);
+        if (lane < 8) s_sum[tile][summed8_index()] = f;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    int u = lane;
+    double f = 0.0;
+    if (thread_reduce(ch, na)) {
+        if (lane < kRows)
+            for (int k = 0; k < ch; ++k) f += s_sum[k][lane];
+    } else {
+        double o[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) o[r] = lane < ch ? 0.0 + s_sum[lane][r] : 0.0;
+        f = lanes_sum8(o, 64);
+        u = summed8_index();
+    }
+    if (lane >= kRows) return;
+    const int64_t st = a.n_act_max;
+    if (u < 3) a.acc[u * st + p] = f;
+    else if (u < 6) a.jerk[(u - 3) * st + p] = f;
+    else if (u == 6 && a.pot) a.pot[p] = f;
+}
+
 hipError_t launch_force(const SweepArgs& a_in, const SweepArgs* ra, int precision, int variant,
                         int grid, bool pot_only, hipStream_t st, const hipEvent_t* marks)
 {
@@ -1392,6 +1465,13 @@ hipError_t launch_force(const SweepArgs& a_in, const SweepArgs* ra, int precisio
     bool refine = !pot_only && ra && a.refine;
     if (a.n_clusters == 1 && !a.n_act_dev) {
         const bool fp64 = make_host_plan(&a, precision, variant, pot_only);
+        if (fp64 && !pot_only && !marks && a.jerk && a.n <= kDirectMax &&
+            a.hp.L == 64 && a.hp.jc == kTJ &&
+            (int64_t)a.hp.n_act * a.n <= kDirectInter) {
+            const int waves = a.hp.s_max < kDirectWaves ? a.hp.s_max : kDirectWaves;
+            hipLaunchKernelGGL(direct_kernel, dim3(a.hp.n_act), dim3(64 * waves), 0, st, a);
+            return hipGetLastError();
+        }
         if (fp64 && refine) {
             // an FP64 block: the plain FP64 sweep and its reduction
             precision = 0;
