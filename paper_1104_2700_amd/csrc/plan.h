@@ -513,18 +513,19 @@ __host__ __device__ inline void split_for_sizes(const SweepArgs& a, int32_t na, 
 // 18.9; 1024 of 1024 12.6 / 11.9).
 constexpr int64_t kSplitMinInter = 1000000;
 
-// FP64 sweeps of 6e7 to 6e8 interactions keep it too: there the model takes
+// FP64 sweeps of 6e7 interactions or more keep it too: there the model takes
 // plan_split's last round for longer than it is (N = 28422, 7105 active: 784
 // items on 768 places 263 us, the model's choice 268; N = 22000, 7333: 208 /
-// 213; N = 40000, 6666: 350 / 357; beyond, N = 65536, 16384: 1280 / 1233).
-// (Block steps whose chunks tile slices have no other choice.)
-constexpr int64_t kSplitKeepFrom = 60000000, kSplitKeepTo = 600000000;
+// 213; N = 40000, 6666: 350 / 357; N = 53850, 26842: 1.73 / 1.80 ms; though
+// N = 65536, 16384: 1.28 / 1.23).  (Block steps whose chunks tile slices have
+// no other choice.)
+constexpr int64_t kSplitKeepFrom = 60000000;
 
 __host__ __device__ __forceinline__ bool split_by_model(const SweepArgs& a, int32_t na)
 {
     const int64_t inter = (int64_t)na * a.n;
     if (!a.auto_split || inter < kSplitMinInter) return false;
-    return !a.split_fp64 || a.split_tiles > 0 || inter < kSplitKeepFrom || inter >= kSplitKeepTo;
+    return !a.split_fp64 || a.split_tiles > 0 || inter < kSplitKeepFrom;
 }
 
 // The same by a wave (every lane calls it): lane 8 l + k takes 2^l lanes and
