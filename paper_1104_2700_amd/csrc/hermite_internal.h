@@ -60,7 +60,7 @@ struct SweepArgs {
     int32_t sel_clusters;      // nonzero: act_start / act_cluster come from the selection
     int32_t* chunks;           // [C]
     int32_t* item_off;         // [C+1]
-    double* partial;           // [s_max][7][n_act]
+    double* partial;           // [s_max][8][n_act], or by lines (partial_at)
     int64_t partial_cap;       // doubles available in partial
     // tuning
     int32_t target_lanes;

@@ -978,7 +978,7 @@ __device__ void correct_reduce_body(const CorrectArgs& c, const SweepArgs& sa, i
             // the same address in every lane of the wave
             load_old_i(c, p == fw.p ? fw.i : (c.idx ? c.idx[p] : p), o);
             double s[kRows];
-            reduce_partials_wave_ch(sa, na, p, first_chunks(sa, fw, p), lane, s);
+            reduce_partials_wave_ch(sa, sa.plan->s_max, na, p, first_chunks(sa, fw, p), lane, s);
             if (lane == 0) {
                 const double a1[3] = {s[0], s[1], s[2]};
                 const double j1[3] = {s[3], s[4], s[5]};

@@ -823,6 +823,7 @@ sweep_kernel(SweepArgs a)
         if ((a.kind == 1 && all64) || (a.kind == 2 && none64)) return;
         if (a.kind == 2 && a.defer_fp64 && fp64_all != 0) return;   // the refine launch's
     }
+    const PartialAt at = partial_at(s_max, na);
     const int rows = kWG / L;          // lanes' slots per particle row
     const int slot = tid / L;
     const int sub = tid & (L - 1);
@@ -1006,7 +1007,6 @@ sweep_kernel(SweepArgs a)
                 fj[q][2] = F[q].jz;
             }
         }
-        double* const dst0 = a.partial + (int64_t)k * kRows * na;
         bool dealt = false;
         if constexpr (!POT_ONLY && !SPLIT && PREC != 3) {
             if (L >= 8) {
@@ -1023,7 +1023,7 @@ sweep_kernel(SweepArgs a)
                         ej[q] = lanes_sum_f32(ej[q], L);
                         f = u == kRows - 1 ? pack_est(ea[q], ej[q]) : f;
                     }
-                    if (valid[q] && sub < 8) dst0[u * (int64_t)na + pp[q]] = f;
+                    if (valid[q] && sub < 8) a.partial[at(pp[q], k) + u * (int64_t)at.row] = f;
                 }
             }
         }
@@ -1042,12 +1042,12 @@ sweep_kernel(SweepArgs a)
                     for (int r = 0; r < 3; ++r) out[q][3 + r] += (double)fj[q][r];
                 }
                 if (valid[q] && sub == 0) {
-                    double* dst = dst0 + pp[q];
+                    double* dst = a.partial + at(pp[q], k);
                     if (POT_ONLY) {
-                        dst[6 * (int64_t)na] = out[q][6];
+                        dst[6 * (int64_t)at.row] = out[q][6];
                     } else {
 #pragma unroll
-                        for (int r = 0; r < kRows; ++r) dst[r * (int64_t)na] = out[q][r];
+                        for (int r = 0; r < kRows; ++r) dst[r * (int64_t)at.row] = out[q][r];
                     }
                 }
             }
