@@ -382,7 +382,8 @@ void fill_refine(const SweepScratch& sc, const SweepArgs& a, int variant, SweepA
 
 // The context's scratch for a sweep of C systems and n_act_max active
 // particles (allocated or grown as needed).
-int ctx_scratch(hermite_ctx* c, int C, int32_t n_act_max, bool refine, SweepScratch* sc)
+int ctx_scratch(hermite_ctx* c, int C, int32_t n_act_max, bool refine, SweepScratch* sc,
+                bool partial = true)
 {
     std::memset(sc, 0, sizeof *sc);
     CHECK(ensure(c, c->plan, sizeof(SweepPlan)));
@@ -390,7 +391,7 @@ int ctx_scratch(hermite_ctx* c, int C, int32_t n_act_max, bool refine, SweepScra
     CHECK(ensure(c, c->act_cnt, sizeof(int32_t) * C));
     CHECK(ensure(c, c->chunks, sizeof(int32_t) * C));
     CHECK(ensure(c, c->item_off, sizeof(int32_t) * (C + 1)));
-    CHECK(ensure(c, c->partial, sizeof(double) * partial_cap_for(n_act_max)));
+    if (partial) CHECK(ensure(c, c->partial, sizeof(double) * partial_cap_for(n_act_max)));
     sc->plan = (SweepPlan*)c->plan.p;
     sc->act_start = (int32_t*)c->act_start.p;
     sc->act_cnt = (int32_t*)c->act_cnt.p;
@@ -426,46 +427,6 @@ int ctx_scratch(hermite_ctx* c, int C, int32_t n_act_max, bool refine, SweepScra
     return HERMITE_OK;
 }
 
-// Fills the sweep arguments and makes sure the context scratch they point
-// to exists (refinement scratch included, when the sweep refines).
-int prepare_sweep(hermite_ctx* c, const hermite_state* s, const hermite_clusters* cl,
-                  const double* xp, const double* vp, const int32_t* idx,
-                  const int32_t* n_act_dev, int32_t n_act_max, double eps2, int precision,
-                  const hermite_tuning& tu, double* acc, double* jerk, double* pot,
-                  SweepArgs* a)
-{
-    const int C = cl ? cl->n_clusters : 1;
-    const double nfac = precision == HERMITE_FP64 ? 0.0 : c->near_factor[precision];
-    const int64_t f64b = precision == HERMITE_FP64 ? 0 : c->fp64_below[precision];
-    const bool refine = uses_refine(precision, cl ? cl->max_size : s->n, f64b);
-    SweepScratch sc;
-    CHECK(ctx_scratch(c, C, n_act_max, refine, &sc));
-    CHECK(ensure(c, c->counters, sizeof(int64_t) * kCounters));
-    fill_sweep(sc, c->n_cu, s, cl, xp, vp, idx, n_act_dev, n_act_max, eps2, precision, tu, nfac, f64b,
-               c->fp64_inter_below[precision], (int64_t*)c->counters.p, acc, jerk, pot, a);
-    return HERMITE_OK;
-}
-
-// The refine sweep's arguments from the context scratch (which
-// prepare_sweep has made for a refining sweep).
-int prepare_refine(hermite_ctx* c, const SweepArgs& a, int variant, SweepArgs* ra)
-{
-    SweepScratch sc;
-    CHECK(ctx_scratch(c, a.n_clusters, a.n_act_max, true, &sc));
-    fill_refine(sc, a, variant, ra);
-    return HERMITE_OK;
-}
-
-// True when the sweep can go by pairs: the host knows that every particle is
-// active (no list, no device count) and every system is swept in FP64.
-bool pairs_fit(const SweepArgs& a, int precision, int n_cu, bool pot_only, PairShape* sh)
-{
-    const bool fp64 = precision == HERMITE_FP64 ||
-                      ((precision == HERMITE_MIXED || precision == HERMITE_MIXED_2F) && !a.refine);
-    return fp64 && !a.idx && !a.n_act_dev && a.n_act_max == a.n && !a.pred_x &&
-           pair_shape(a.n, a.n_clusters, a.n_cmax, n_cu, pot_only, sh);
-}
-
 // The context's partial sums of a pair sweep, or false where they cannot be
 // had (more than kPairMaxBytes, no memory, or a stream under capture that
 // would need an allocation): the one-sided sweep, whose scratch exists, then
@@ -498,6 +459,58 @@ bool pair_scratch(hermite_ctx* c, int64_t doubles, hipStream_t st)
     c->pair.p = p;
     c->pair.bytes = need;
     return true;
+}
+
+// Fills the sweep arguments and makes sure the context scratch they point
+// to exists (refinement scratch included, when the sweep refines).  pairs:
+// the caller goes on to run_force on stream st, with pot_only (kPairsPot) or
+// not (kPairsForce); where that goes by pairs, only the pairs' partial sums
+// are made.
+enum { kPairsNo, kPairsForce, kPairsPot };
+
+int prepare_sweep(hermite_ctx* c, const hermite_state* s, const hermite_clusters* cl,
+                  const double* xp, const double* vp, const int32_t* idx,
+                  const int32_t* n_act_dev, int32_t n_act_max, double eps2, int precision,
+                  const hermite_tuning& tu, double* acc, double* jerk, double* pot,
+                  SweepArgs* a, int pairs = kPairsNo, hipStream_t st = nullptr)
+{
+    const int C = cl ? cl->n_clusters : 1;
+    const int64_t n_cmax = cl ? cl->max_size : s->n;
+    const double nfac = precision == HERMITE_FP64 ? 0.0 : c->near_factor[precision];
+    const int64_t f64b = precision == HERMITE_FP64 ? 0 : c->fp64_below[precision];
+    const bool refine = uses_refine(precision, n_cmax, f64b);
+    PairShape sh;
+    const bool by_pairs =
+        pairs != kPairsNo && !idx && !n_act_dev && n_act_max == s->n && !refine &&
+        precision != HERMITE_MIXED_SP &&
+        pair_shape(s->n, C, n_cmax, c->n_cu, pairs == kPairsPot, &sh) &&
+        pair_scratch(c, pair_partial_doubles(sh, s->n, n_cmax, pairs == kPairsPot), st);
+    SweepScratch sc;
+    CHECK(ctx_scratch(c, C, n_act_max, refine, &sc, !by_pairs));
+    CHECK(ensure(c, c->counters, sizeof(int64_t) * kCounters));
+    fill_sweep(sc, c->n_cu, s, cl, xp, vp, idx, n_act_dev, n_act_max, eps2, precision, tu, nfac, f64b,
+               c->fp64_inter_below[precision], (int64_t*)c->counters.p, acc, jerk, pot, a);
+    return HERMITE_OK;
+}
+
+// The refine sweep's arguments from the context scratch (which
+// prepare_sweep has made for a refining sweep).
+int prepare_refine(hermite_ctx* c, const SweepArgs& a, int variant, SweepArgs* ra)
+{
+    SweepScratch sc;
+    CHECK(ctx_scratch(c, a.n_clusters, a.n_act_max, true, &sc));
+    fill_refine(sc, a, variant, ra);
+    return HERMITE_OK;
+}
+
+// True when the sweep can go by pairs: the host knows that every particle is
+// active (no list, no device count) and every system is swept in FP64.
+bool pairs_fit(const SweepArgs& a, int precision, int n_cu, bool pot_only, PairShape* sh)
+{
+    const bool fp64 = precision == HERMITE_FP64 ||
+                      ((precision == HERMITE_MIXED || precision == HERMITE_MIXED_2F) && !a.refine);
+    return fp64 && !a.idx && !a.n_act_dev && a.n_act_max == a.n && !a.pred_x &&
+           pair_shape(a.n, a.n_clusters, a.n_cmax, n_cu, pot_only, sh);
 }
 
 int run_force(hermite_ctx* c, const SweepArgs& a, int precision, const hermite_tuning& tu,
@@ -985,7 +998,7 @@ int hermite_force_jerk(hermite_ctx* c, const hermite_state* s, const hermite_clu
     SweepArgs a;
     const hermite_tuning& tu = c->tuning[precision];
     CHECK(prepare_sweep(c, s, cl, s->xp, s->vp, idx, n_act_dev, n_act_max, eps2, precision, tu, acc,
-                        jerk, pot, &a));
+                        jerk, pot, &a, kPairsForce, (hipStream_t)stream));
     return run_force(c, a, precision, tu, false, (hipStream_t)stream);
 }
 
@@ -1157,7 +1170,7 @@ int hermite_initialize(hermite_ctx* c, const hermite_state* s, const hermite_clu
     SweepArgs a;
     const hermite_tuning& tu = c->tuning[precision];
     CHECK(prepare_sweep(c, s, cl, s->xp, s->vp, nullptr, nullptr, (int32_t)s->n, eps2, precision, tu,
-                        s->a, s->j, s->pot, &a));
+                        s->a, s->j, s->pot, &a, kPairsForce, st));
     CHECK(run_force(c, a, precision, tu, false, st));
     HIP_OK(launch_init_dt(s->n, s->tick_bits, s->a, s->j, s->t, s->dt, p->eta, p->form,
                           p->eta_init, p->k_min, p->k_max, (int64_t*)c->counters.p, st));
@@ -1178,7 +1191,7 @@ int hermite_energy(hermite_ctx* c, const hermite_state* s, const hermite_cluster
     SweepArgs a;
     const hermite_tuning& tu = c->tuning[HERMITE_FP64];
     CHECK(prepare_sweep(c, s, cl, s->x, s->v, nullptr, nullptr, (int32_t)s->n, eps2, HERMITE_FP64, tu,
-                        phi, nullptr, phi, &a));
+                        phi, nullptr, phi, &a, kPairsPot, st));
     a.counters = nullptr;
     CHECK(run_force(c, a, HERMITE_FP64, tu, true, st));
     HIP_OK(launch_energy_reduce(s->n, cl ? cl->n_clusters : 1, cl ? cl->offsets : nullptr,
