@@ -113,18 +113,21 @@ __device__ __forceinline__ void sum_step(double (&o)[7])
 }
 
 // The plan of every block size: log2 (lanes) | 8 log2 (tiles of a chunk), or
-// kNoPlan where the chunks do not tile a slice or have no room.
+// kNoPlan where the chunks do not tile a slice or have no room.  A wave a
+// size (a thread a size: 70 us at N = 16384, its divisions one after another).
 constexpr int kNoPlan = 255;
 __global__ void __launch_bounds__(kWG) mid_plan_kernel(MidRunArgs e, SweepArgs sa)
 {
-    const int na = (int)(blockIdx.x * kWG + threadIdx.x) + 1;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int na = (int)blockIdx.x * (kWG / 64) + wave + 1;
     if (na > (int)sa.n) return;
     int32_t L, ti;
     int64_t jc;
-    plan_split(sa, na, 1, &L, &ti, &jc);
-    if (e.model && split_by_model(sa, na)) split_for_sizes(sa, na, &L, &jc);
+    plan_split_wave(sa, na, 1, &L, &ti, &jc);
+    if (e.model && split_by_model(sa, na)) split_for_sizes_wave(sa, na, &L, &ti, &jc);
     const bool ok = jc <= kMidSlice && kMidSlice % jc == 0 &&
                     (int64_t)((na + e.rows - 1) / e.rows) * (kMidSlice / jc) <= e.partial_lines;
+    if ((threadIdx.x & 63) != 0) return;
     e.plans[na] = ok ? (uint8_t)((31 - __clz(L)) | (31 - __clz((int)(jc / kTJ))) << 3)
                      : (uint8_t)kNoPlan;
 }
@@ -760,8 +763,8 @@ hipError_t launch_mid_run(const SmallRunArgs& r, const MidRunArgs& e, const Swee
                           hipStream_t st)
 {
     const dim3 grid(e.rows * e.slices), wg(kMidThreads);
-    hipLaunchKernelGGL(mid_plan_kernel, dim3((unsigned)((r.n + kWG - 1) / kWG)), dim3(kWG), 0, st,
-                       e, sa);
+    hipLaunchKernelGGL(mid_plan_kernel, dim3((unsigned)((r.n + kWG / 64 - 1) / (kWG / 64))),
+                       dim3(kWG), 0, st, e, sa);
     hipLaunchKernelGGL(mid_run_kernel, grid, wg, 0, st, r, e);
     return hipGetLastError();
 }

@@ -487,9 +487,8 @@ __host__ __device__ inline bool split_lanes_ok(const SweepArgs& a, int32_t na, i
     return L == 64 || (int64_t)a.ipl * (kWG / L) <= 2 * (int64_t)na;
 }
 
-// The split of least modelled time.
-__host__ __device__ inline void split_for_sizes(const SweepArgs& a, int32_t na, int32_t* L_io,
-                                                int64_t* jc_io)
+// The split of least modelled time (host).
+inline void split_for_sizes(const SweepArgs& a, int32_t na, int32_t* L_io, int64_t* jc_io)
 {
     const int32_t L_plan = *L_io;
     float best = 3.0e38f;
