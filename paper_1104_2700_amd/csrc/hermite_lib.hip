@@ -4,6 +4,7 @@
 #include "hermite_internal.h"
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -1347,11 +1348,12 @@ int hermite_small_run_launches(hermite_ctx* c, int64_t out[3])
     return HERMITE_OK;
 }
 
-// Who may hold a device's compute units for many steps: up to four launches
-// of launch_small_run (64 workgroups each, and a process has four hardware
-// queues), or one of launch_mid_run (a workgroup a unit).  More would wait
-// for each other's places; who does not get in takes single steps.
+// Who may hold a device's compute units for many steps: as many launches of
+// launch_small_run (64 workgroups each) as have a unit for every workgroup,
+// or one of launch_mid_run (a workgroup a unit).  More would wait for each
+// other's places; who does not get in takes single steps.
 static std::shared_mutex g_chip[64];
+static std::atomic<int> g_small_runs[64];
 
 // Launches r (r.steps and the verdict's numbers set here) until the run is
 // over or is to be taken step by step.
@@ -1464,7 +1466,14 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
         return run_launches(c, r, 65536, &c->small_epoch, max_steps, st, launched, steps,
                             interactions, done, ended, [&](bool* in) -> int {
             std::shared_lock<std::shared_mutex> chip(g_chip[c->device], std::try_to_lock);
-            if (!(*in = chip.owns_lock())) return HERMITE_OK;
+            struct Place {
+                std::atomic<int>& n;
+                int before;
+                explicit Place(std::atomic<int>& k) : n(k), before(k.fetch_add(1)) {}
+                ~Place() { n.fetch_sub(1); }
+            } place(g_small_runs[c->device]);
+            *in = chip.owns_lock() && (place.before + 1) * kSmallRunGrid <= c->n_cu;
+            if (!*in) return HERMITE_OK;
             HIP_OK(launch_small_run(r, st));
             HIP_OK(hipStreamSynchronize(st));
             return HERMITE_OK;
