@@ -163,7 +163,7 @@ pair_sweep_kernel(SweepArgs a, PairShape sh, uint32_t* queue)
         // ---- the item: cluster c, block ab, chunk ch ------------------------
         int64_t cb = 0, ce = n;
         int ab, ch, nb;
-        double eps2 = a.eps2;
+        double eps2 = a.eps2_c ? a.eps2_c[0] : a.eps2;   // one system, or one cluster
         if (many) {
             const int c = upper_bound_i32(a.item_off, a.n_clusters + 1, item) - 1;
             cb = a.offsets[c];

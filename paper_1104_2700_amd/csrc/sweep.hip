@@ -1405,6 +1405,7 @@ __global__ void __launch_bounds__(64 * kDirectWaves) direct_kernel(SweepArgs a)
     const int n = (int)a.n, na = a.hp.n_act, ch = a.hp.s_max, p = (int)blockIdx.x;
     count_host_plan(a);
     const int i = a.idx ? a.idx[p] : p;
+    const double eps2 = a.eps2_c ? a.eps2_c[0] : a.eps2;   // one system, or one cluster
     I64 I;
     SumD A;
     for (int tile = wave; tile < ch; tile += waves) {
@@ -1428,7 +1429,7 @@ __global__ void __launch_bounds__(64 * kDirectWaves) direct_kernel(SweepArgs a)
         B.zero();
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            pair_f64<true>(I, a.eps2, x[k][0], x[k][1], x[k][2], v[k][0], v[k][1], v[k][2], m[k],
+            pair_f64<true>(I, eps2, x[k][0], x[k][1], x[k][2], v[k][0], v[k][1], v[k][2], m[k],
                            off[k], B);
         A.add(B);
         const double o[kRows] = {A.ax, A.ay, A.az, A.jx, A.jy, A.jz, -A.pp, 0.0};

@@ -1,0 +1,64 @@
+"""Ensembles of one cluster: the same calls on one system, with the softening
+that the cluster states (the scalar argument is then not used), through every
+kernel that a call of one system may take: small blocks (up to 6400
+particles), full sweeps one-sided and by pairs (from 6000 particles on,
+potentials from 4500), block steps.
+
+The two calls make the same sums, so they agree to the FP64 bar of 1e-13
+(here: of the largest value), and block steps after a few steps to the same."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+EPS2 = 0.04          # far from the scalar's 0: another softening is another result
+
+
+@pytest.fixture(scope="module")
+def H():
+    from paper_1104_2700_amd import hermite
+    return hermite
+
+
+@pytest.fixture(scope="module")
+def ctx(H):
+    c = H.Context(0)
+    yield c
+    c.close()
+
+
+def _pair(H, n, seed=0):
+    from paper_1104_2700_amd import inputs
+    x, v, m = inputs.plummer(n, 40 + n + seed)
+    s = H.State(x, v, m)
+    s.xp.copy_(s.x)
+    s.vp.copy_(s.v)
+    return s, H.Clusters(np.array([0, n], dtype=np.int64), np.array([EPS2]))
+
+
+def _close(got, ref):
+    for a, b in zip(got, ref):
+        assert float((a - b).abs().max()) <= 1e-13 * float(b.abs().max())
+
+
+@pytest.mark.parametrize("n", [900, 4499, 4500, 5999, 6000, 6400, 6401, 20001])
+def test_softening(H, ctx, n):
+    from paper_1104_2700_amd import inputs
+    s, cl = _pair(H, n)
+    idx = torch.from_numpy(inputs.random_active(n, 77, 5)).cuda()
+    for which in (None, idx):
+        _close(ctx.force_jerk(s, which, 0.0, H.FP64, clusters=cl),
+               [o.clone() for o in ctx.force_jerk(s, which, EPS2, H.FP64)])
+        na = n if which is None else 77
+        out = [torch.empty(k, dtype=torch.float64, device="cuda") for k in ((3, na), (3, na), (na,))]
+        H.force_jerk_noalloc(s, which, 0.0, H.FP64, *out, clusters=cl)
+        _close(out, ctx.force_jerk(s, which, EPS2, H.FP64))
+    _close([ctx.energy(s, 0.0, clusters=cl).flatten()], [ctx.energy(s, EPS2).flatten()])
+    params = H.dt_params(0.02, H.DT_PAPER, 3, 20)
+    one = s.clone()
+    ctx.initialize(s, EPS2, params, H.FP64)
+    ctx.initialize(one, 0.0, params, H.FP64, clusters=cl)
+    _close((one.a, one.j, one.pot), (s.a, s.j, s.pot))
+    assert torch.equal(one.dt, s.dt)
