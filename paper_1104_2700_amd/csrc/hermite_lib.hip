@@ -305,7 +305,7 @@ void fill_sweep(const SweepScratch& sc, int n_cu, const hermite_state* s, const 
     a->offsets = cl ? cl->offsets : nullptr;
     a->eps2_c = cl ? cl->eps2 : nullptr;
     a->eps2 = eps2;
-    a->n_cmax = cl ? cl->max_size : s->n;
+    a->n_cmax = a->n_clusters > 1 ? cl->max_size : s->n;
     a->plan = sc.plan;
     a->act_start = sc.act_start;
     a->act_cnt = sc.act_cnt;
@@ -318,7 +318,7 @@ void fill_sweep(const SweepScratch& sc, int n_cu, const hermite_state* s, const 
     a->n_cu = n_cu;
     const hermite_tuning def = default_tuning_for(n_cu);
     a->auto_split = std::memcmp(&tu, &def, sizeof def) == 0 ? 1 : 0;
-    if (a->auto_split && !cl) {
+    if (a->auto_split && a->n_clusters == 1) {   // (one cluster is planned as a system is)
         const bool mixed = precision == HERMITE_MIXED || precision == HERMITE_MIXED_2F;
         const bool small = mixed && s->n < fp64_below;   // swept in FP64
         set_split_model(a, small ? HERMITE_FP64 : precision, small ? tu.variant & 1 : tu.variant,
@@ -476,7 +476,7 @@ int prepare_sweep(hermite_ctx* c, const hermite_state* s, const hermite_clusters
                   SweepArgs* a, int pairs = kPairsNo, hipStream_t st = nullptr)
 {
     const int C = cl ? cl->n_clusters : 1;
-    const int64_t n_cmax = cl ? cl->max_size : s->n;
+    const int64_t n_cmax = C > 1 ? cl->max_size : s->n;
     const double nfac = precision == HERMITE_FP64 ? 0.0 : c->near_factor[precision];
     const int64_t f64b = precision == HERMITE_FP64 ? 0 : c->fp64_below[precision];
     const bool refine = uses_refine(precision, n_cmax, f64b);

@@ -62,3 +62,38 @@ def test_softening(H, ctx, n):
     ctx.initialize(one, 0.0, params, H.FP64, clusters=cl)
     _close((one.a, one.j, one.pot), (s.a, s.j, s.pot))
     assert torch.equal(one.dt, s.dt)
+
+
+@pytest.mark.parametrize("n,n_act", [(1200, 1200), (2500, 2000), (33000, 2000), (40000, 1300)])
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+def test_plans(H, ctx, prec, n, n_act):
+    """From 1e6 interactions on, where a default tuning's split is chosen by
+    a model of the sweep's time: plans made on the host and on the device
+    (a count in device memory), in every precision (mixed from 32768
+    particles and 5e7 interactions on).  The same plans: the same bits."""
+    from paper_1104_2700_amd import inputs
+    s, cl = _pair(H, n, 1)
+    idx = torch.from_numpy(inputs.random_active(n, n_act, 5)).cuda()
+    count = torch.tensor([n_act], dtype=torch.int32, device="cuda")
+    for dev in (None, count):
+        ref = [o.clone() for o in ctx.force_jerk(s, idx, EPS2, prec, n_act_dev=dev)]
+        got = ctx.force_jerk(s, idx, 0.0, prec, n_act_dev=dev, clusters=cl)
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b)
+            assert torch.isfinite(a).all()
+
+
+@pytest.mark.parametrize("prec", [0, 1, 3])
+@pytest.mark.parametrize("n", [1000, 2500, 17000, 33000])
+def test_block_steps(H, ctx, prec, n):
+    """A few steps, from a block of every particle on (the steps start equal)."""
+    s, cl = _pair(H, n, 2)
+    params = H.dt_params(0.02, H.DT_PAPER, 3, 20)
+    ctx.initialize(s, EPS2, params, prec)
+    s.dt.fill_(1 << 10)
+    one = s.clone()
+    for _ in range(3):
+        ctx.step(s, EPS2, params, prec)
+        ctx.step(one, 0.0, params, prec, clusters=cl)
+    _close((one.x, one.v), (s.x, s.v))
+    assert torch.equal(one.t, s.t)
