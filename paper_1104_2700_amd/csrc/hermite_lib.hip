@@ -671,8 +671,8 @@ int enqueue_step(hermite_ctx* c, const hermite_state* s, const hermite_clusters*
     int64_t* T = (int64_t*)c->step_T.p;
     double* out = (double*)c->step_out.p;
     int64_t* counters = (int64_t*)c->counters.p;
-    // one system in a run: the active block is the prefix of the order
-    int32_t* aidx = (level && !cl) ? (int32_t*)c->lvl_perm.p : idx;
+    // one system (or cluster) in a run: the active block is the prefix of the order
+    int32_t* aidx = (level && (!cl || cl->n_clusters == 1)) ? (int32_t*)c->lvl_perm.p : idx;
     SweepArgs a;
     const hermite_tuning& tu = c->tuning[precision];
     CHECK(prepare_sweep(c, s, cl, s->xp, s->vp, aidx, na, (int32_t)n, eps2, precision, tu, out,

@@ -97,3 +97,22 @@ def test_block_steps(H, ctx, prec, n):
         ctx.step(one, 0.0, params, prec, clusters=cl)
     _close((one.x, one.v), (s.x, s.v))
     assert torch.equal(one.t, s.t)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 3])
+@pytest.mark.parametrize("n", [1000, 2500, 17000, 33000])
+def test_runs(H, ctx, prec, n):
+    """A run selects its blocks from the step-size order, as one system's
+    does, and integrates to the same state."""
+    s, cl = _pair(H, n, 2)
+    params = H.dt_params(0.02, H.DT_PAPER, 3, 20)
+    ctx.initialize(s, EPS2, params, prec)
+    for graph in (True, False):
+        ref, one = s.clone(), s.clone()
+        for _ in range(20):
+            ctx.step(ref, EPS2, params, prec)
+        steps, inter = ctx.run(one, 0.0, params, 1 << 20, prec, clusters=cl, use_graph=graph,
+                               max_steps=20)
+        assert steps == 20 and inter > 0
+        _close((one.x, one.v), (ref.x, ref.v))
+        assert torch.equal(one.t, ref.t)
