@@ -1906,7 +1906,7 @@ int hermite_autotune(hermite_ctx* c, const hermite_state* s, const hermite_clust
         rc = run(best, 1, &us, nullptr);
         if (rc != HERMITE_OK) break;
         SweepPlan P;
-        if (!cl) {
+        if (!cl || cl->n_clusters == 1) {   // made on the host
             SweepArgs a;
             rc = prepare_sweep(c, s, cl, s->xp, s->vp, idx, nullptr, n_act, eps2, precision, best,
                                out, out + 3 * (size_t)n_act, out + 6 * (size_t)n_act, &a);

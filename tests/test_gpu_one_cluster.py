@@ -116,3 +116,18 @@ def test_runs(H, ctx, prec, n):
         assert steps == 20 and inter > 0
         _close((one.x, one.v), (ref.x, ref.v))
         assert torch.equal(one.t, ref.t)
+
+
+def test_autotune_reports_its_plan(H, tmp_path):
+    """The partial sums that the chosen shape writes and reads: a whole number
+    of chunks of eight doubles a particle, twice."""
+    n, n_act = 3000, 64
+    s, cl = _pair(H, n, 3)
+    c = H.Context(0)
+    try:
+        c.autotune(s, 0.0, H.FP64, n_act=n_act, cache_path=tmp_path / "t.json", clusters=cl)
+    finally:
+        c.close()
+    text = (tmp_path / "t.json").read_text()
+    chunks = float(text.split('"partial_bytes":')[1].split("}")[0]) / (2 * 64 * n_act)
+    assert chunks == int(chunks) and 1 <= chunks <= 12   # tiles of 256 particles
