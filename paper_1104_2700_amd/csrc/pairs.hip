@@ -96,7 +96,22 @@ constexpr int64_t kPairMaxN = (int64_t)1 << 23;   // rows of at most 2^15 - 1 ti
 constexpr int64_t kPairMaxCluster = 8192, kPairMeanCluster = 256;
 constexpr double kPairEnsemble = 6.0e7, kPairManyEnsemble = 4.0e7;
 constexpr int kPairMany = 30;
-constexpr int kPairClusterSlots = 16;
+constexpr int kPairClusterSlots = 17;
+
+// Two levels of sums, as in the one-sided sweep: a register adds a run of at
+// most 256 terms, and the runs are added up by themselves.  Workgroups of
+// K = 4 have long chunks (2816 terms at N = 65536): each tile's sums go to a
+// second sum, in LDS.  Those of K = 3 have no LDS to spare (16 KB instead of 7
+// leave 9 workgroups a unit for 12: N = 9973 110 -> 124 us), so their chunks
+// end after four tiles of 64.  (Root mean square error of the acceleration,
+// one-sided / by pairs in one level / in two: N = 65536 1.47 / 2.25 / 1.40e-16,
+// 100000 1.42 / 3.22 / 1.36e-16, 44000 1.62 / 2.13 / 1.44e-16; times as with
+// one level: 65536 3.20 / 3.19 ms, 9973 113.9 / 114.8 us.)
+constexpr int kPairRun = 4;
+__host__ __device__ constexpr bool pair_two_levels(int k, bool pot_only)
+{
+    return pot_only || k > 3;
+}
 
 // One particle of the sweep: coordinates (velocities), mass, sums.
 template <bool POT>
@@ -152,6 +167,10 @@ pair_sweep_kernel(SweepArgs a, PairShape sh, uint32_t* queue)
     constexpr int NC = PairI<POT>::NC, NS = PairI<POT>::NS;
     __shared__ double jc[NC + 1][kJT];   // coordinates and mass of the tile
     __shared__ double js[NS][kJT];       // its sums
+    // the i-side sums' second level, a lane its own: acc and jerk here, the
+    // potential in a register (seven rows leave no room for a second workgroup)
+    constexpr bool kTop = pair_two_levels(K, POT), kTopLds = kTop && !POT;
+    __shared__ double s_top[kTopLds ? NS - 1 : 1][kTopLds ? kBI : 1];
     __shared__ int32_t s_item;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -185,7 +204,7 @@ pair_sweep_kernel(SweepArgs a, PairShape sh, uint32_t* queue)
             const int64_t ib = cb + (int64_t)ab * kBI;
             const int icnt = (int)(ce - ib < kBI ? ce - ib : kBI);
             const bool busy = wave * K * 64 < icnt;   // this wave holds a particle
-            double ci[K][NC], mi[K], si[K][NS];
+            double ci[K][NC], mi[K], si[K][NS], top[K];
 #pragma unroll
             for (int q = 0; q < K; ++q) {
                 const int k = (wave * K + q) * 64 + lane;
@@ -199,6 +218,11 @@ pair_sweep_kernel(SweepArgs a, PairShape sh, uint32_t* queue)
                 mi[q] = ok ? a.m[g] : 0.0;
 #pragma unroll
                 for (int r = 0; r < NS; ++r) si[q][r] = 0.0;
+                top[q] = 0.0;
+                if constexpr (kTopLds) {
+#pragma unroll
+                    for (int r = 0; r < NS - 1; ++r) s_top[r][k] = 0.0;
+                }
             }
             for (int u = u0; u < u1; ++u) {
                 const int dist = u / K, t = u - dist * K;
@@ -239,39 +263,53 @@ pair_sweep_kernel(SweepArgs a, PairShape sh, uint32_t* queue)
                             }
                         }
                     }
-                    continue;
-                }
-                for (int ph = 0; ph < W; ++ph) {
-                    const int sub = (wave + ph) % W;
-                    if (busy && sub * 64 < cnt) {
-                        for (int s = 0; s < 64; ++s) {
-                            const int p = sub * 64 + ((lane + s) & 63);
-                            double cj[NC], sj[NS];
+                } else {
+                    for (int ph = 0; ph < W; ++ph) {
+                        const int sub = (wave + ph) % W;
+                        if (busy && sub * 64 < cnt) {
+                            for (int s = 0; s < 64; ++s) {
+                                const int p = sub * 64 + ((lane + s) & 63);
+                                double cj[NC], sj[NS];
 #pragma unroll
-                            for (int d = 0; d < NC; ++d) cj[d] = jc[d][p];
-                            const double mj = jc[NC][p];
+                                for (int d = 0; d < NC; ++d) cj[d] = jc[d][p];
+                                const double mj = jc[NC][p];
 #pragma unroll
-                            for (int r = 0; r < NS; ++r) sj[r] = 0.0;
+                                for (int r = 0; r < NS; ++r) sj[r] = 0.0;
 #pragma unroll
-                            for (int q = 0; q < K; ++q) {
-                                double d[NC], ri, ri3 = 0.0;
-                                pair_shared<POT>(cj, ci[q], eps2, d, ri);
-                                pair_finish<POT>(d, ri, ri3);
-                                pair_side<POT>(mj, d, ri, ri3, si[q]);
-                                pair_side<POT>(mi[q], d, ri, ri3, sj);
+                                for (int q = 0; q < K; ++q) {
+                                    double d[NC], ri, ri3 = 0.0;
+                                    pair_shared<POT>(cj, ci[q], eps2, d, ri);
+                                    pair_finish<POT>(d, ri, ri3);
+                                    pair_side<POT>(mj, d, ri, ri3, si[q]);
+                                    pair_side<POT>(mi[q], d, ri, ri3, sj);
+                                }
+#pragma unroll
+                                for (int r = 0; r < NS; ++r) unsafeAtomicAdd(&js[r][p], sj[r]);
                             }
-#pragma unroll
-                            for (int r = 0; r < NS; ++r) unsafeAtomicAdd(&js[r][p], sj[r]);
                         }
+                        __syncthreads();   // the next wave's turn at this part
                     }
-                    __syncthreads();   // the next wave's turn at this part
-                }
-                if (tid < cnt) {
-                    // the j side saw -r and -v: acc and jerk change sign, as
-                    // the potential -m/r does
-                    double* dst = a.partial + (int64_t)(sh.nch + dist - 1) * NS * n + jb + tid;
+                    if (tid < cnt) {
+                        // the j side saw -r and -v: acc and jerk change sign, as
+                        // the potential -m/r does
+                        double* dst = a.partial + (int64_t)(sh.nch + dist - 1) * NS * n + jb + tid;
 #pragma unroll
-                    for (int r = 0; r < NS; ++r) dst[(int64_t)r * n] = -js[r][tid];
+                        for (int r = 0; r < NS; ++r) dst[(int64_t)r * n] = -js[r][tid];
+                    }
+                }
+                if constexpr (kTop) {   // the tile's sums to the second level
+#pragma unroll
+                    for (int q = 0; q < K; ++q) {
+                        if constexpr (kTopLds) {
+#pragma unroll
+                            for (int r = 0; r < NS - 1; ++r) {
+                                s_top[r][(wave * K + q) * 64 + lane] += si[q][r];
+                                si[q][r] = 0.0;
+                            }
+                        }
+                        top[q] += si[q][NS - 1];
+                        si[q][NS - 1] = 0.0;
+                    }
                 }
             }
 #pragma unroll
@@ -280,8 +318,9 @@ pair_sweep_kernel(SweepArgs a, PairShape sh, uint32_t* queue)
                 if (k < icnt) {
                     double* dst = a.partial + (int64_t)ch * NS * n + ib + k;
 #pragma unroll
-                    for (int r = 0; r < NS; ++r)
-                        dst[(int64_t)r * n] = r == NS - 1 ? -si[q][r] : si[q][r];
+                    for (int r = 0; r < NS - 1; ++r)
+                        dst[(int64_t)r * n] = kTopLds ? s_top[kTopLds ? r : 0][kTopLds ? k : 0] : si[q][r];
+                    dst[(int64_t)(NS - 1) * n] = -(kTop ? top[q] : si[q][NS - 1]);
                 }
             }
         }
@@ -325,7 +364,8 @@ __global__ void __launch_bounds__(kWG) pair_plan_kernel(SweepArgs a, PairShape s
 }
 
 // Adds every particle's partial sums: kGroups threads a particle, each the
-// slots g, g + kGroups, ... in order, then the groups in order.
+// slots g, g + kGroups, ... two at a time (half the roundings at the sum's
+// size), then the groups in pairs.
 template <bool POT>
 __global__ void __launch_bounds__(kWG) pair_reduce_kernel(SweepArgs a, PairShape sh)
 {
@@ -364,10 +404,7 @@ __global__ void __launch_bounds__(kWG) pair_reduce_kernel(SweepArgs a, PairShape
                 v1[r] = q1[(int64_t)r * n];
             }
 #pragma unroll
-            for (int r = 0; r < NS; ++r) {
-                s[r] += v0[r];
-                s[r] += k2 < cnt ? v1[r] : 0.0;
-            }
+            for (int r = 0; r < NS; ++r) s[r] += v0[r] + (k2 < cnt ? v1[r] : 0.0);
         }
     }
     if (g > 0) {
@@ -378,11 +415,9 @@ __global__ void __launch_bounds__(kWG) pair_reduce_kernel(SweepArgs a, PairShape
     if (a.n_clusters == 1 && a.counters && blockIdx.x == 0 && tid == 0)
         atomicAdd((unsigned long long*)&a.counters[1], (unsigned long long)(n * n));
     if (g > 0 || p >= n) return;
+    static_assert(kGroups == 4, "added in pairs");
 #pragma unroll
-    for (int q = 0; q < kGroups - 1; ++q) {
-#pragma unroll
-        for (int r = 0; r < NS; ++r) s[r] += s_s[q][r][l];
-    }
+    for (int r = 0; r < NS; ++r) s[r] = (s[r] + s_s[0][r][l]) + (s_s[1][r][l] + s_s[2][r][l]);
     if constexpr (POT) {
         a.pot[p] = s[0];
     } else {
@@ -401,12 +436,13 @@ __global__ void __launch_bounds__(kWG) pair_reduce_kernel(SweepArgs a, PairShape
 // unit do not advance evenly: the older one is served first, and one left
 // alone on its unit reaches about 0.7 of the pair rate.  N = 65536: 3.24 ms
 // with these levels, 3.70 ms with 512 equal items for 512 places.)
-void guided_levels(PairShape* sh, int u, int nb, int slots, double share)
+void guided_levels(PairShape* sh, int u, int nb, int slots, double share, int longest)
 {
     for (int qmin = 1;; ++qmin) {
         int c = 0, done = 0;
         while (done < u && c < kPairMaxLevels) {
-            const int q = std::max(qmin, (int)std::ceil((double)(u - done) * nb / (slots * share)));
+            const int q = std::max(
+                qmin, std::min(longest, (int)std::ceil((double)(u - done) * nb / (slots * share))));
             sh->lev[c++] = (int16_t)done;
             done += std::min(q, u - done);
         }
@@ -438,7 +474,8 @@ bool pair_shape(int64_t n, int n_clusters, int64_t n_cmax, int n_cu, bool pot_on
         sh->bi = 64 * sh->k * sh->w;
         const int u = pair_row(pair_blocks(n_cmax, sh->bi), 0, sh->k);
         const int fill = (int)(inter / (2.0 * sh->bi * 64) / (16.0 * n_cu)) + 1;
-        const int q = std::max(std::min(fill, 4), (u + kPairClusterSlots - 1) / kPairClusterSlots);
+        const int q = std::max(std::min(fill, kPairRun),
+                               (u + kPairClusterSlots - 1) / kPairClusterSlots);
         int c = 0;
         for (int done = 0; done < u; done += q) sh->lev[c++] = (int16_t)done;
         sh->nch = c;
@@ -451,7 +488,8 @@ bool pair_shape(int64_t n, int n_clusters, int64_t n_cmax, int n_cu, bool pot_on
     sh->bi = 64 * sh->k * sh->w;
     const int nb = pair_blocks(n, sh->bi);
     guided_levels(sh, pair_row(nb, 0, sh->k), nb, n_cu * (8 / sh->w),
-                  sh->w == 4 || pot_only ? 1.5 : 1.0);
+                  sh->w == 4 || pot_only ? 1.5 : 1.0,
+                  pair_two_levels(sh->k, pot_only) ? INT32_MAX : kPairRun);
     sh->items = nb * sh->nch;
     return true;
 }
