@@ -83,7 +83,8 @@ struct hermite_ctx {
     // per-cluster tables and partial sums, and the flagging reduce's ticket
     Buf ref_pos, ref_idx, ref_p, ref_tmp, ref_ucnt, ref_ccnt, rplan, ract_start, ract_cnt,
         rchunks, ritem_off;
-    Buf pair;   // full FP64 sweeps by pairs: the queue word, then the partial sums
+    int64_t partial_cap = 0;   // doubles of `partial` that plans may use
+    Buf pair;   // full FP64 sweeps by pairs whose partial sums do not fit `partial`
     Buf sel_min, sel_cnt;
     Buf step_idx, step_na, step_T, step_out, step_acl, phi, counters, ticket, flag;
     // step-size order of a run (hermite_run)
@@ -277,6 +278,20 @@ int64_t partial_cap_for(int32_t n_act_max)
     return (int64_t)kRows * 32 * std::max<int64_t>(n_act_max, 4096);
 }
 
+size_t partial_bytes_for(int32_t n_act_max)
+{
+    return sizeof(double) * (size_t)partial_cap_for(n_act_max);
+}
+
+size_t pair_bytes(const PairShape& sh, int64_t n, int64_t n_cmax, bool pot_only)
+{
+    return sizeof(double) * (size_t)pair_partial_doubles(sh, n, n_cmax, pot_only);
+}
+
+// The pairs' queue word lies behind the plan.
+constexpr size_t kPlanSlot = 256;
+static_assert(sizeof(SweepPlan) <= kPlanSlot, "plan slot");
+
 // True when a sweep of this precision and these systems runs the FP64
 // refinement: the mixed precisions, when some system is swept in FP32.
 bool uses_refine(int precision, int64_t n_cmax, int64_t fp64_below)
@@ -383,23 +398,29 @@ void fill_refine(const SweepScratch& sc, const SweepArgs& a, int variant, SweepA
 
 // The context's scratch for a sweep of C systems and n_act_max active
 // particles (allocated or grown as needed).
-int ctx_scratch(hermite_ctx* c, int C, int32_t n_act_max, bool refine, SweepScratch* sc,
-                bool partial = true)
+int ctx_scratch(hermite_ctx* c, int C, int32_t n_act_max, bool refine, SweepScratch* sc)
 {
     std::memset(sc, 0, sizeof *sc);
-    CHECK(ensure(c, c->plan, sizeof(SweepPlan)));
+    CHECK(ensure(c, c->plan, kPlanSlot + sizeof(uint32_t)));   // and the pairs' queue
     CHECK(ensure(c, c->act_start, sizeof(int32_t) * C));
     CHECK(ensure(c, c->act_cnt, sizeof(int32_t) * C));
     CHECK(ensure(c, c->chunks, sizeof(int32_t) * C));
     CHECK(ensure(c, c->item_off, sizeof(int32_t) * (C + 1)));
-    if (partial) CHECK(ensure(c, c->partial, sizeof(double) * partial_cap_for(n_act_max)));
+    CHECK(ensure(c, c->partial, partial_bytes_for(n_act_max)));
     sc->plan = (SweepPlan*)c->plan.p;
     sc->act_start = (int32_t*)c->act_start.p;
     sc->act_cnt = (int32_t*)c->act_cnt.p;
     sc->chunks = (int32_t*)c->chunks.p;
     sc->item_off = (int32_t*)c->item_off.p;
     sc->partial = (double*)c->partial.p;
-    sc->partial_cap = (int64_t)(c->partial.bytes / sizeof(double));
+    // plans follow the capacity that the largest call so far asked for, also
+    // where the pairs' partial sums made the buffer larger; a captured step
+    // follows that of its capture
+    if (partial_cap_for(n_act_max) > c->partial_cap) {
+        drop_graphs(c);
+        c->partial_cap = partial_cap_for(n_act_max);
+    }
+    sc->partial_cap = c->partial_cap;
     if (refine) {
         const size_t na = (size_t)std::max<int32_t>(n_act_max, 1);
         CHECK(ensure(c, c->ref_pos, sizeof(int32_t) * na));
@@ -428,52 +449,54 @@ int ctx_scratch(hermite_ctx* c, int C, int32_t n_act_max, bool refine, SweepScra
     return HERMITE_OK;
 }
 
-// The context's partial sums of a pair sweep, or false where they cannot be
-// had (more than kPairMaxBytes, no memory, or a stream under capture that
+// The partial sums of a sweep by pairs (need bytes), or null where they cannot
+// be had (more than kPairMaxBytes, no memory, or a stream under capture that
 // would need an allocation): the one-sided sweep, whose scratch exists, then
-// does the work.  No captured step refers to this buffer.
+// does the work.  They are in c->partial where that is large enough
+// (prepare_sweep makes it so when it has to be made or grown anyway), else in
+// a buffer of their own.
 constexpr int64_t kPairMaxBytes = (int64_t)4 << 30;
 
-constexpr size_t kPairHead = 256;
-
-bool pair_scratch(hermite_ctx* c, int64_t doubles, hipStream_t st)
+double* pair_scratch(hermite_ctx* c, size_t need, hipStream_t st)
 {
-    const size_t need = kPairHead + sizeof(double) * (size_t)doubles;
-    if ((int64_t)need > kPairMaxBytes) return false;
-    if (c->pair.bytes >= need) return true;
+    if (c->partial.bytes >= need) return (double*)c->partial.p;
+    if ((int64_t)need > kPairMaxBytes) return nullptr;
+    if (c->pair.bytes >= need) return (double*)c->pair.p;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return nullptr;
     }
-    if (cap != hipStreamCaptureStatusNone) return false;
+    if (cap != hipStreamCaptureStatusNone) return nullptr;
     if (c->pair.p) {
-        if (hipDeviceSynchronize() != hipSuccess) return false;
+        if (hipDeviceSynchronize() != hipSuccess) return nullptr;
         (void)hipFree(c->pair.p);
         c->pair = Buf();
     }
     void* p = nullptr;
     if (hipMalloc(&p, need) != hipSuccess || !p) {
         (void)hipGetLastError();
-        return false;
+        return nullptr;
     }
     c->pair.p = p;
     c->pair.bytes = need;
-    return true;
+    return (double*)c->pair.p;
 }
 
 // Fills the sweep arguments and makes sure the context scratch they point
 // to exists (refinement scratch included, when the sweep refines).  pairs:
-// the caller goes on to run_force on stream st, with pot_only (kPairsPot) or
-// not (kPairsForce); where that goes by pairs, only the pairs' partial sums
-// are made.
+// the caller goes on to run_force, with pot_only (kPairsPot) or not
+// (kPairsForce); where that goes by pairs and the partial sums have to be
+// made or grown, they are made large enough for the pairs' (one allocation in
+// a first call).  They are made for the one-sided sweep in any case: a later
+// call under capture, which cannot allocate, may be of that kind.
 enum { kPairsNo, kPairsForce, kPairsPot };
 
 int prepare_sweep(hermite_ctx* c, const hermite_state* s, const hermite_clusters* cl,
                   const double* xp, const double* vp, const int32_t* idx,
                   const int32_t* n_act_dev, int32_t n_act_max, double eps2, int precision,
                   const hermite_tuning& tu, double* acc, double* jerk, double* pot,
-                  SweepArgs* a, int pairs = kPairsNo, hipStream_t st = nullptr)
+                  SweepArgs* a, int pairs = kPairsNo)
 {
     const int C = cl ? cl->n_clusters : 1;
     const int64_t n_cmax = C > 1 ? cl->max_size : s->n;
@@ -481,13 +504,16 @@ int prepare_sweep(hermite_ctx* c, const hermite_state* s, const hermite_clusters
     const int64_t f64b = precision == HERMITE_FP64 ? 0 : c->fp64_below[precision];
     const bool refine = uses_refine(precision, n_cmax, f64b);
     PairShape sh;
-    const bool by_pairs =
-        pairs != kPairsNo && !idx && !n_act_dev && n_act_max == s->n && !refine &&
-        precision != HERMITE_MIXED_SP &&
-        pair_shape(s->n, C, n_cmax, c->n_cu, pairs == kPairsPot, &sh) &&
-        pair_scratch(c, pair_partial_doubles(sh, s->n, n_cmax, pairs == kPairsPot), st);
+    if (pairs != kPairsNo && !idx && !n_act_dev && n_act_max == s->n && !refine &&
+        precision != HERMITE_MIXED_SP && c->partial.bytes < partial_bytes_for(n_act_max) &&
+        pair_shape(s->n, C, n_cmax, c->n_cu, pairs == kPairsPot, &sh)) {
+        const size_t both = std::max(partial_bytes_for(n_act_max),
+                                     pair_bytes(sh, s->n, n_cmax, pairs == kPairsPot));
+        if ((int64_t)both <= kPairMaxBytes && ensure(c, c->partial, both) != HERMITE_OK)
+            (void)ensure(c, c->partial, partial_bytes_for(n_act_max));
+    }
     SweepScratch sc;
-    CHECK(ctx_scratch(c, C, n_act_max, refine, &sc, !by_pairs));
+    CHECK(ctx_scratch(c, C, n_act_max, refine, &sc));
     CHECK(ensure(c, c->counters, sizeof(int64_t) * kCounters));
     fill_sweep(sc, c->n_cu, s, cl, xp, vp, idx, n_act_dev, n_act_max, eps2, precision, tu, nfac, f64b,
                c->fp64_inter_below[precision], (int64_t*)c->counters.p, acc, jerk, pot, a);
@@ -518,12 +544,14 @@ int run_force(hermite_ctx* c, const SweepArgs& a, int precision, const hermite_t
               bool pot_only, hipStream_t st, const hipEvent_t* marks = nullptr)
 {
     PairShape sh;
-    if (pairs_fit(a, precision, c->n_cu, pot_only, &sh) &&
-        pair_scratch(c, pair_partial_doubles(sh, a.n, a.n_cmax, pot_only), st)) {
+    if (pairs_fit(a, precision, c->n_cu, pot_only, &sh)) {
         SweepArgs b = a;
-        b.partial = (double*)((char*)c->pair.p + kPairHead);
-        HIP_OK(launch_pairs(b, sh, (uint32_t*)c->pair.p, c->n_cu, pot_only, st, marks));
-        return HERMITE_OK;
+        b.partial = pair_scratch(c, pair_bytes(sh, a.n, a.n_cmax, pot_only), st);
+        if (b.partial) {
+            uint32_t* queue = (uint32_t*)((char*)c->plan.p + kPlanSlot);
+            HIP_OK(launch_pairs(b, sh, queue, c->n_cu, pot_only, st, marks));
+            return HERMITE_OK;
+        }
     }
     const int grid = std::max(1, c->n_cu * tu.wg_per_cu);
     SweepArgs ra;
@@ -999,7 +1027,7 @@ int hermite_force_jerk(hermite_ctx* c, const hermite_state* s, const hermite_clu
     SweepArgs a;
     const hermite_tuning& tu = c->tuning[precision];
     CHECK(prepare_sweep(c, s, cl, s->xp, s->vp, idx, n_act_dev, n_act_max, eps2, precision, tu, acc,
-                        jerk, pot, &a, kPairsForce, (hipStream_t)stream));
+                        jerk, pot, &a, kPairsForce));
     return run_force(c, a, precision, tu, false, (hipStream_t)stream);
 }
 
@@ -1022,7 +1050,7 @@ int hermite_force_jerk_timed(hermite_ctx* c, const hermite_state* s, const hermi
     SweepArgs a;
     const hermite_tuning& tu = c->tuning[precision];
     CHECK(prepare_sweep(c, s, cl, s->xp, s->vp, idx, nullptr, n_act, eps2, precision, tu, acc,
-                        jerk, pot, &a));
+                        jerk, pot, &a, kPairsForce));
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     int rc = HERMITE_OK;
     double sum[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1171,7 +1199,7 @@ int hermite_initialize(hermite_ctx* c, const hermite_state* s, const hermite_clu
     SweepArgs a;
     const hermite_tuning& tu = c->tuning[precision];
     CHECK(prepare_sweep(c, s, cl, s->xp, s->vp, nullptr, nullptr, (int32_t)s->n, eps2, precision, tu,
-                        s->a, s->j, s->pot, &a, kPairsForce, st));
+                        s->a, s->j, s->pot, &a, kPairsForce));
     CHECK(run_force(c, a, precision, tu, false, st));
     HIP_OK(launch_init_dt(s->n, s->tick_bits, s->a, s->j, s->t, s->dt, p->eta, p->form,
                           p->eta_init, p->k_min, p->k_max, (int64_t*)c->counters.p, st));
@@ -1192,7 +1220,7 @@ int hermite_energy(hermite_ctx* c, const hermite_state* s, const hermite_cluster
     SweepArgs a;
     const hermite_tuning& tu = c->tuning[HERMITE_FP64];
     CHECK(prepare_sweep(c, s, cl, s->x, s->v, nullptr, nullptr, (int32_t)s->n, eps2, HERMITE_FP64, tu,
-                        phi, nullptr, phi, &a, kPairsPot, st));
+                        phi, nullptr, phi, &a, kPairsPot));
     a.counters = nullptr;
     CHECK(run_force(c, a, HERMITE_FP64, tu, true, st));
     HIP_OK(launch_energy_reduce(s->n, cl ? cl->n_clusters : 1, cl ? cl->offsets : nullptr,
