@@ -84,7 +84,11 @@ struct hermite_ctx {
     Buf ref_pos, ref_idx, ref_p, ref_tmp, ref_ucnt, ref_ccnt, rplan, ract_start, ract_cnt,
         rchunks, ritem_off;
     int64_t partial_cap = 0;   // doubles of `partial` that plans may use
-    Buf pair;   // full FP64 sweeps by pairs whose partial sums do not fit `partial`
+    // full FP64 sweeps by pairs whose partial sums do not fit `partial`; those
+    // of before that a captured call may still use
+    Buf pair;
+    bool pair_captured = false;
+    std::vector<Buf> pair_kept;
     Buf sel_min, sel_cnt;
     Buf step_idx, step_na, step_T, step_out, step_acl, phi, counters, ticket, flag;
     // step-size order of a run (hermite_run)
@@ -454,32 +458,42 @@ int ctx_scratch(hermite_ctx* c, int C, int32_t n_act_max, bool refine, SweepScra
 // would need an allocation): the one-sided sweep, whose scratch exists, then
 // does the work.  They are in c->partial where that is large enough
 // (prepare_sweep makes it so when it has to be made or grown anyway), else in
-// a buffer of their own.
+// a buffer of their own.  A caller may have captured a call on that buffer: it
+// is then kept until the context goes, and the larger one is made beside it.
 constexpr int64_t kPairMaxBytes = (int64_t)4 << 30;
 
 double* pair_scratch(hermite_ctx* c, size_t need, hipStream_t st)
 {
     if (c->partial.bytes >= need) return (double*)c->partial.p;
     if ((int64_t)need > kPairMaxBytes) return nullptr;
-    if (c->pair.bytes >= need) return (double*)c->pair.p;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
-    if (cap != hipStreamCaptureStatusNone) return nullptr;
-    if (c->pair.p) {
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    if (c->pair.bytes >= need) {
+        c->pair_captured = c->pair_captured || capturing;
+        return (double*)c->pair.p;
+    }
+    if (capturing) return nullptr;
+    size_t kept = need;
+    for (const Buf& b : c->pair_kept) kept += b.bytes;
+    if (c->pair_captured && (int64_t)(kept + c->pair.bytes) > kPairMaxBytes) return nullptr;
+    Buf grown;
+    if (c->pair.p && !c->pair_captured) {
         if (hipDeviceSynchronize() != hipSuccess) return nullptr;
         (void)hipFree(c->pair.p);
         c->pair = Buf();
     }
-    void* p = nullptr;
-    if (hipMalloc(&p, need) != hipSuccess || !p) {
+    if (hipMalloc(&grown.p, need) != hipSuccess || !grown.p) {
         (void)hipGetLastError();
         return nullptr;
     }
-    c->pair.p = p;
-    c->pair.bytes = need;
+    grown.bytes = need;
+    if (c->pair.p) c->pair_kept.push_back(c->pair);
+    c->pair = grown;
+    c->pair_captured = false;
     return (double*)c->pair.p;
 }
 
@@ -969,6 +983,7 @@ int hermite_destroy(hermite_ctx* c)
                    &c->lvl_ccnt, &c->lvl_ccum, &c->lvl_cna, &c->lvl_bits};
     for (Buf* b : bufs)
         if (b->p) (void)hipFree(b->p);
+    for (Buf& b : c->pair_kept) (void)hipFree(b.p);
     if (c->small_status) (void)hipHostFree(c->small_status);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     delete c;

@@ -1,5 +1,6 @@
 """Calls under capture, which cannot allocate: after one call on a system of a
-size, another call on it is captured whatever its kind."""
+size, another call on it is captured whatever its kind, and what was captured
+stays valid when later calls make the sweep by pairs' scratch grow."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -74,6 +75,31 @@ def test_a_call_is_captured_after_another_kind(H, ctx, warm, block, prec):
         _replays(g, out, ref, warm_up)
     finally:
         other.close()
+
+
+def test_a_captured_sweep_by_pairs_outlives_the_scratchs_growth(H, ctx):
+    """The scratch of both kinds, made by a call with a list and by one
+    without; then larger ones."""
+    n = 8000
+    s, eps2 = _state(H, n)
+    ident = torch.arange(n, dtype=torch.int32, device="cuda")
+    ctx.force_jerk(s, ident, eps2, H.FP64)
+    ref = [o.clone() for o in ctx.force_jerk(s, None, eps2, H.FP64)]
+    out = _outputs(n)
+    g = _capture(ctx, s, None, eps2, H.FP64, out)
+    held = []
+
+    def grow(k=[12000, 17000, 24000]):
+        if not k:
+            return
+        big, e2 = _state(H, k.pop(0))
+        ctx.force_jerk(big, torch.arange(big.n, dtype=torch.int32, device="cuda"), e2, H.FP64)
+        ctx.force_jerk(big, None, e2, H.FP64)
+        held.append(torch.full((1 << 22,), float("nan"), device="cuda"))   # whoever gets freed memory
+
+    _replays(g, out, ref, grow)
+    for a, b in zip(out, ref):
+        assert torch.equal(a, b)
 
 
 def test_bits_do_not_depend_on_a_sweep_by_pairs_before(H):
