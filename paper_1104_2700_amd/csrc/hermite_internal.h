@@ -360,9 +360,9 @@ struct SmallRunArgs {
 constexpr int kSmallRunRec = 13;      // x, v, a, j and the new step
 constexpr int kSmallRunLine = 16;     // int64 per flag (a 128-byte line)
 
-// True when a run of this system may go by launch_small_run: the plan of
-// every block has 64 lanes a particle and chunks of one tile.
-bool small_run_fits(const SweepArgs& a);
+// True when the plans of this system's blocks are launch_small_run's: 64
+// lanes a particle and chunks of one tile, whatever the active count.
+bool small_run_plans(const SweepArgs& a);
 hipError_t launch_small_run(const SmallRunArgs& r, hipStream_t st);
 
 // The same for one system beyond kSmallRunMax particles (midrun.hip).

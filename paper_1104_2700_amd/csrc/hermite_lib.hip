@@ -109,8 +109,8 @@ struct hermite_ctx {
     // grid of the fused select + sweep for the last shape it was sized for
     struct {
         int64_t n = -1, cap = 0;
-        int32_t lanes = 0, min_j = 0, ipl = 0, grid = 0;
-        bool small_run = false;
+        int32_t lanes = 0, min_j = 0, ipl = 0, one_chunk = 0, grid = 0;
+        bool small_plans = false;
     } fused;
 };
 
@@ -670,21 +670,22 @@ int level_init(hermite_ctx* c, const hermite_state* s, const hermite_clusters* c
     return HERMITE_OK;
 }
 
-// Sizes the fused select + sweep for a's system (once per shape): the grid
-// that any active count fills at most, returned, and whether whole runs may
-// go by launch_small_run.
+// Sizes the fused select + sweep for a's system (once per shape, all that the
+// plans of its blocks depend on): the grid that any active count fills at
+// most, returned, and whether every plan is one for launch_small_run.
 int32_t size_fused(hermite_ctx* c, const SweepArgs& a)
 {
     auto& f = c->fused;
     if (f.n != a.n || f.cap != a.partial_cap || f.lanes != a.target_lanes ||
-        f.min_j != a.min_j_per_lane || f.ipl != a.ipl) {
+        f.min_j != a.min_j_per_lane || f.ipl != a.ipl || f.one_chunk != a.one_chunk) {
         f.n = a.n;
         f.cap = a.partial_cap;
         f.lanes = a.target_lanes;
         f.min_j = a.min_j_per_lane;
         f.ipl = a.ipl;
+        f.one_chunk = a.one_chunk;
         f.grid = max_plan_items(a);
-        f.small_run = small_run_fits(a);
+        f.small_plans = small_run_plans(a);
     }
     return f.grid;
 }
@@ -1464,12 +1465,13 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
     tile_slices(&a);
     const bool mid = n > kSmallRunMax;
     MidRunShape shape = {};
+    if (!a.auto_split) return HERMITE_OK;   // the default tuning only
     if (mid) {
         shape = mid_run_shape(n, c->n_cu);
-        if (!a.auto_split || shape.rows < 2) return HERMITE_OK;
+        if (shape.rows < 2) return HERMITE_OK;
     } else {
         (void)size_fused(c, a);
-        if (!c->fused.small_run) return HERMITE_OK;
+        if (!c->fused.small_plans) return HERMITE_OK;
     }
     if (!c->small_status)
         HIP_OK(hipHostMalloc((void**)&c->small_status, sizeof(SmallRunStatus), hipHostMallocDefault));

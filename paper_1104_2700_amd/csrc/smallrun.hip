@@ -366,9 +366,9 @@ __global__ void __launch_bounds__(64 * MAXW, 1) small_run_kernel(SmallRunArgs r)
 
 }  // namespace
 
-bool small_run_fits(const SweepArgs& a)
+bool small_run_plans(const SweepArgs& a)
 {
-    if (a.n_clusters != 1 || a.n > kSmallRunMax || !a.auto_split) return false;
+    if (a.n_clusters != 1 || a.n > kSmallRunMax) return false;
     // every block's plan: 64 lanes a particle, chunks of one tile
     for (int32_t na = 1; na <= (int32_t)a.n; ++na) {
         int32_t L, ti;
