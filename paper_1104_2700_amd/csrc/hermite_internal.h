@@ -384,7 +384,9 @@ struct MidRunShape {
     int64_t partial_lines;
 };
 
-// Exchange buffers (words, zeroed before their first use: no tag is 0).
+// Exchange buffers (words, zeroed before their first use: no tag is 0).  Their
+// places follow n, so a word may hold what another size's run left: always a
+// word with a tag of that run's, never used again.
 struct MidRunArgs {
     int slices, rows;
     uint32_t rows_inverse;    // ceil(2^32 / rows)
@@ -395,7 +397,7 @@ struct MidRunArgs {
     uint64_t* all_due;        // [2][slices slice] lines
     uint64_t* partial;        // [rows slices][partial_lines] lines
     uint64_t* corrected;      // [slices slice] pairs of lines
-    uint8_t* plans;           // [n + 1]
+    uint8_t* plans;           // [n + 1], apart from the words
     int64_t* verdict;
 };
 

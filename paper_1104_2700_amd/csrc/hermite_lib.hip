@@ -1535,7 +1535,10 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
     const size_t row = 2 * grid * kMidRowSlots * line;
     const size_t all = 2 * (size_t)e.slices * kMidSlice * line;
     const size_t part = grid * (size_t)e.partial_lines * line;
-    const size_t bytes = head + row + all + part + all + (size_t)n + 1;
+    // the plans first, at the same place for every n: words without a tag may
+    // never lie where a larger system polls for one
+    const size_t plans = ((size_t)kMidRunMax + 1 + line - 1) / line * line;
+    const size_t bytes = plans + head + row + all + part + all;
     const bool grown = c->mid_x.bytes < bytes || !c->mid_flag.p;
     // (without the memory for it: single steps)
     if (ensure(c, c->mid_x, bytes) != HERMITE_OK) return HERMITE_OK;
@@ -1544,13 +1547,13 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
         HIP_OK(hipMemsetAsync(c->mid_x.p, 0, c->mid_x.bytes, st));
         HIP_OK(hipMemsetAsync(c->mid_flag.p, 0, sizeof(int64_t), st));
     }
-    unsigned char* base = (unsigned char*)c->mid_x.p;
+    e.plans = (uint8_t*)c->mid_x.p;
+    unsigned char* base = (unsigned char*)c->mid_x.p + plans;
     e.header = (uint64_t*)base;
     e.row_due = (uint64_t*)(base + head);
     e.all_due = (uint64_t*)(base + head + row);
     e.partial = (uint64_t*)(base + head + row + all);
     e.corrected = (uint64_t*)(base + head + row + all + part);
-    e.plans = base + head + row + all + part + all;
     e.verdict = (int64_t*)c->mid_flag.p;
     return run_launches(c, r, 4096, &c->mid_epoch, max_steps, st, launched, steps, interactions,
                         done, ended, [&](bool* in) -> int {
