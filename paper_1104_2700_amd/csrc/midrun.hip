@@ -190,7 +190,7 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
     int64_t T = 0, inter = 0, done_steps = 0, last_T = 0;
     int32_t na = 0, last_na = 0, clamped = 0, bad = 0, handoff = 0;
     bool gave_up = s_stop != 0;
-    int32_t to_check = r.check_every + 1;
+    int32_t to_check = r.check_every;
     // z / P, z < 65536
     auto by_rows = [&](int z) { return (int)__umulhi((uint32_t)z, e.rows_inverse); };
 
@@ -199,8 +199,8 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
         const int par = (int)(step & 1);
         // ---- this slice's earliest time and its due particles ----------------
         int32_t wrong = 0;
-        if (--to_check == 0) {
-            to_check = r.check_every;
+        if (to_check-- == 0) {   // before step check_every + 1, 2 check_every + 1, ...
+            to_check = r.check_every - 1;
             wrong = __syncthreads_or(non_finite(x, v, a, jk) ? 1 : 0) ? 1 : 0;
         }
         int64_t en[KP], mn = INT64_MAX;

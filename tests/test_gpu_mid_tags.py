@@ -84,3 +84,15 @@ def test_plans_are_never_taken_for_words(runs):
         runs.check(n)
     runs.advance(0x06060606 - STEPS // 2, n=2048)
     runs.check(16384)
+
+
+def test_the_longest_interval_between_checks(runs):
+    """sync_every = 2^31 - 1: one launch, checked at its end."""
+    n = 1600
+    s0, eps2, ref = runs._system(n)
+    s = s0.clone()
+    runs.ctx.run(s, eps2, runs.params, 1 << TB, runs.H.FP64, sync_every=(1 << 31) - 1,
+                 max_steps=STEPS)
+    torch.cuda.synchronize()
+    for key in KEYS:
+        assert torch.equal(getattr(s, key), getattr(ref, key)), key
