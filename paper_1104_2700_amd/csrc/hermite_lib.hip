@@ -1413,6 +1413,7 @@ static int run_launches(hermite_ctx* c, SmallRunArgs& r, int64_t launch_steps, i
         r.epoch = *epoch;
         r.launch = ++c->small_launch;
         *epoch += r.steps + 2;
+        std::memset(c->small_status, 0, sizeof *c->small_status);   // (no launch is under way)
         bool in = false;
         CHECK(launch(&in));
         if (!in) return HERMITE_OK;
