@@ -317,6 +317,15 @@ hipError_t launch_correct_reduce(const CorrectArgs& c, const SweepArgs& sa, hipS
 constexpr int kSmallRunMax = 1536;       // particles
 constexpr int kSmallRunGrid = 64;        // workgroups
 
+// How long the workgroups of a launch of many steps wait for each other, in
+// ticks of the 100 MHz wall clock.  On a free chip all of them start within
+// tens of microseconds; where others hold compute units, the run goes on in
+// single steps after 10 ms (three of the longest sweeps of 65536 particles),
+// with nothing lost.  Once all have started, only a preempted process keeps a
+// word away for more than microseconds, and the launch's steps would be lost:
+// two seconds, longer than a time slice.
+constexpr int64_t kRunArrival = 1000000, kRunPatience = 200000000;
+
 // What a launch did; in pinned host memory, written by the kernel's end.
 struct SmallRunStatus {
     int64_t launch;      // the launch that wrote it
@@ -351,7 +360,9 @@ struct SmallRunArgs {
     int64_t* flags;           // [kSmallRunGrid] on lines of their own, then the verdict
     int64_t epoch;            // flags count from here (never reused)
     int64_t launch;           // verdicts are 2 launch (commit) or 2 launch + 1 (given up)
-    int64_t patience;         // wall clock ticks a workgroup waits for the others
+    int64_t arrival;          // wall clock ticks a workgroup waits for the others'
+                              // first word: until all have started
+    int64_t patience;         // and for any later one
     int64_t* counters;
     int32_t* na_out;
     int64_t* T_out;

@@ -102,9 +102,8 @@ struct hermite_ctx {
     Buf mid_x, mid_flag;   // the same for runs by launch_mid_run
     int64_t mid_epoch = 1;
     int64_t runs_on_chip = 0, runs_given_up = 0, runs_handed_off = 0;
-    // how long their workgroups wait for each other: two seconds of the
-    // 100 MHz wall clock
-    int64_t small_patience = 200000000;
+    // how long their workgroups wait for all of them to have started
+    int64_t small_arrival = kRunArrival;
     std::vector<GraphEntry> graphs;
     // grid of the fused select + sweep for the last shape it was sized for
     struct {
@@ -1372,12 +1371,12 @@ int hermite_block_histogram(hermite_ctx* c, int64_t out[33], void* stream)
 }
 
 // Not part of the ABI: sets how long (wall clock ticks) the workgroups of a
-// small system's run wait for each other before the launch is given up
-// (negative: it gives up at once).  For the tests of what follows then.
+// launch of many steps wait for all of them to have started before it is given
+// up (negative: it gives up at once).  For the tests of what follows then.
 int hermite_small_run_patience(hermite_ctx* c, int64_t ticks)
 {
     if (!c) return fail(HERMITE_EINVAL, "null context");
-    c->small_patience = ticks;
+    c->small_arrival = ticks;
     return HERMITE_OK;
 }
 
@@ -1495,7 +1494,8 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
     r.k_max = p->k_max;
     r.T_end = T_end;
     r.check_every = sync_every;
-    r.patience = c->small_patience;
+    r.arrival = c->small_arrival;
+    r.patience = r.arrival < 0 ? r.arrival : kRunPatience;
     r.counters = (int64_t*)c->counters.p;
     r.na_out = (int32_t*)c->step_na.p;
     r.T_out = (int64_t*)c->step_T.p;

@@ -55,6 +55,8 @@ static_assert(kMidMaxSlices <= 16, "16 lanes for the slices' sums");
 
 struct Spin {            // a bounded wait
     int64_t patience;
+    const int64_t* verdict;
+    int64_t launch;
     int64_t t0 = 0;
     int k = 0;
     __device__ bool over()
@@ -62,7 +64,7 @@ struct Spin {            // a bounded wait
         if (++k < 256) return false;
         const int64_t now = wall_clock64();
         if (t0 == 0) t0 = now;
-        return now - t0 > patience;
+        return now - t0 > patience || given_up(verdict, launch);
     }
 };
 
@@ -274,7 +276,7 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
         }
         // ---- every workgroup's header ------------------------------------------
         if (tid < grid) {
-            Spin spin{r.patience};
+            Spin spin{step == 1 ? r.arrival : r.patience, e.verdict, r.launch};
             uint64_t w[1], lo[1], hi[1];
             bool ok = take(hdr + its_word, tag, spin, w);
             const int qq = place(tid) - p * Q;
@@ -327,7 +329,7 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
                 const uint64_t* w = s < kMidRowSlots
                     ? e.row_due + (((int64_t)par * grid + p * Q + sl) * kMidRowSlots + s) * kMidLine
                     : e.all_due + ((int64_t)par * Q * S + S * sl + s) * kMidLine;
-                Spin spin{r.patience};
+                Spin spin{r.patience, e.verdict, r.launch};
                 uint64_t u[13];
                 if (!take(w, tag, spin, u)) s_stop = 1;
 #pragma unroll
@@ -483,7 +485,7 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
                     }
                 }
             }
-            Spin spin{r.patience};
+            Spin spin{r.patience, e.verdict, r.launch};
             if (by_thread) {
                 const int s = tid >> 3, u = tid & 7;
                 if (s < cnt && u < 7) {
@@ -616,7 +618,7 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
                 const int cnt = min(kRecs, my_na - b0);
                 __syncthreads();
                 const uint64_t* w = e.corrected + ((int64_t)S * q + b0) * 2 * kMidLine;
-                Spin spin{r.patience};
+                Spin spin{r.patience, e.verdict, r.launch};
                 for (int i = tid; i < cnt * 2 * kMidLine; i += 4 * kMidThreads) {
                     uint64_t u[4];
                     for (;;) {
@@ -688,7 +690,7 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
         if (tid == 0) put(hdr + my_word, (uint32_t)wrong, tag);
         uint64_t w[1] = {0};
         if (tid < grid) {
-            Spin spin{r.patience};
+            Spin spin{r.patience, e.verdict, r.launch};
             if (!take(hdr + its_word, tag, spin, w)) s_stop = 1;
         }
         bad |= __syncthreads_or((int)((uint32_t)w[0] & 1u)) ? 1 : 0;

@@ -45,6 +45,12 @@ __device__ __forceinline__ double quad_value(double v, int e)
     return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
 }
 
+// Whether a workgroup has given the launch up (who waits for it then does too).
+__device__ __forceinline__ bool given_up(const int64_t* verdict, int64_t launch)
+{
+    return get(verdict) == 2 * launch + 1;
+}
+
 // The launch's verdict: the first word set for it stands.
 __device__ inline bool settle(int64_t* verdict, int64_t launch, bool commit)
 {

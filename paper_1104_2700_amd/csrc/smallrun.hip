@@ -21,8 +21,8 @@
 // 2.3 us without the fences (measured alone; 16 workgroups 2.25, 8 on one XCD
 // 1.7).
 //
-// No wait is without end: a workgroup that waits longer than `patience`
-// gives up, and the launch with it.  Whether the launch counts is settled by
+// No wait is without end: a workgroup that waits longer than `arrival` in the
+// first step, or `patience` later, gives up, and the launch with it.  Whether the launch counts is settled by
 // one word that the first to know sets (all steps done by all, or given up);
 // only then is anything of the state but the potentials written, so a launch
 // that was given up leaves the state as it was and the host takes the steps
@@ -45,8 +45,9 @@ static_assert(kSmallRunMax == 6 * kTJ, "at most six waves");
 constexpr int kMaxSlots = kSmallRunMax / kSmallRunGrid;
 
 // One wave: waits until every workgroup's flag is at least `want`.  False
-// when that takes longer than `patience` (at once when that is negative).
-__device__ bool wait_all(const int64_t* flags, int64_t want, int64_t patience)
+// when that takes longer than `patience` (at once when that is negative) or
+// another workgroup has given up.
+__device__ bool wait_all(const int64_t* flags, int64_t want, int64_t patience, int64_t launch)
 {
     const int lane = threadIdx.x & 63;
     static_assert(kSmallRunGrid == 64, "one flag a lane");
@@ -56,7 +57,9 @@ __device__ bool wait_all(const int64_t* flags, int64_t want, int64_t patience)
         if (__all(get(f) >= want)) return true;
     const int64_t t0 = wall_clock64();
     while (!__all(get(f) >= want))
-        if (wall_clock64() - t0 > patience) return false;
+        if (wall_clock64() - t0 > patience ||
+            __any(given_up(flags + kSmallRunGrid * kSmallRunLine, launch)))
+            return false;
     return true;
 }
 
@@ -270,7 +273,9 @@ __global__ void __launch_bounds__(64 * MAXW, 1) small_run_kernel(SmallRunArgs r)
             if (lane == 0)
                 __hip_atomic_store(&r.flags[g * kSmallRunLine], r.epoch + step, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-            if (!wait_all(r.flags, r.epoch + step, r.patience) && lane == 0) s_stop = 1;
+            if (!wait_all(r.flags, r.epoch + step, step == 1 ? r.arrival : r.patience, r.launch) &&
+                lane == 0)
+                s_stop = 1;
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
         __syncthreads();
@@ -313,7 +318,7 @@ __global__ void __launch_bounds__(64 * MAXW, 1) small_run_kernel(SmallRunArgs r)
             if (lane == 0)
                 __hip_atomic_store(&r.flags[g * kSmallRunLine], r.epoch + r.steps + 1,
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            ok = wait_all(r.flags, r.epoch + r.steps + 1, r.patience);
+            ok = wait_all(r.flags, r.epoch + r.steps + 1, r.patience, r.launch);
         }
         if (lane == 0) s_stop = settle(&r.flags[kSmallRunGrid * kSmallRunLine], r.launch, ok) ? 0 : 1;
     }

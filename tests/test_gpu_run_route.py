@@ -3,6 +3,7 @@ of them (launches, of these given up, of these ended before a block they
 cannot take): so that the comparisons with single steps compare two things."""
 import ctypes
 import threading
+import time
 
 import pytest
 
@@ -75,6 +76,24 @@ def test_a_launch_without_patience_is_given_up_and_counted(H, ctx, n):
     a = _run(H, ctx, *args)
     assert _launches(H, ctx) == (1, 1, 0)
     _same(a, _run(H, ctx, *args, graph=False))
+
+
+@pytest.mark.parametrize("n", [300, 1536, 4000, 16384])
+def test_a_launch_given_up_by_some_ends_for_all(H, ctx, n):
+    """Next to no time to start: a workgroup may give up while others, that
+    saw all of them, go on to the next exchange, where they wait for seconds.
+    They learn of it, and single steps give the run's result."""
+    args = _start(H, ctx, n)
+    ref = _run(H, ctx, *args, graph=False)
+    f = H.lib.hermite_small_run_patience
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int64]
+    begin = time.perf_counter()
+    for ticks in (0, 30, 100, 300, 1000, 3000):
+        assert f(ctx.h, ticks) == H.OK
+        for _ in range(3):
+            _same(_run(H, ctx, *args), ref)
+    assert time.perf_counter() - begin < 1.5   # 18 runs of milliseconds; one long wait is 2 s
+    assert _launches(H, ctx)[0] == 18 and _launches(H, ctx)[2] == 0
 
 
 def test_systems_of_both_kinds_in_turn_on_one_context(H, ctx):
