@@ -336,7 +336,6 @@ struct SmallRunStatus {
     int64_t T;           // the last block time selected (> T_end: the end)
     int64_t na;          // its active particles (0 past T_end)
     int64_t bad;         // a non-finite value was found
-    int64_t handoff;     // the next block is not one for these launches
 };
 
 struct SmallRunArgs {

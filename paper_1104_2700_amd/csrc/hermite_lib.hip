@@ -101,7 +101,7 @@ struct hermite_ctx {
     int64_t small_epoch = 0, small_launch = 0;
     Buf mid_x, mid_flag;   // the same for runs by launch_mid_run
     int64_t mid_epoch = 1;
-    int64_t runs_on_chip = 0, runs_given_up = 0, runs_handed_off = 0;
+    int64_t runs_on_chip = 0, runs_given_up = 0;
     // how long their workgroups wait for all of them to have started
     int64_t small_arrival = kRunArrival;
     std::vector<GraphEntry> graphs;
@@ -1380,14 +1380,15 @@ int hermite_small_run_patience(hermite_ctx* c, int64_t ticks)
     return HERMITE_OK;
 }
 
-// Not part of the ABI: launches of many block steps so far, how many of them
-// were given up, and how many ended before a block they cannot take.
+// Not part of the ABI: launches of many block steps so far, and how many of
+// them were given up (a third word stays 0).  For the tests of which runs go
+// by such launches.
 int hermite_small_run_launches(hermite_ctx* c, int64_t out[3])
 {
     if (!c) return fail(HERMITE_EINVAL, "null context");
     out[0] = c->runs_on_chip;
     out[1] = c->runs_given_up;
-    out[2] = c->runs_handed_off;
+    out[2] = 0;
     return HERMITE_OK;
 }
 
@@ -1419,17 +1420,17 @@ static int run_launches(hermite_ctx* c, SmallRunArgs& r, int64_t launch_steps, i
         const SmallRunStatus h = *c->small_status;
         if (h.launch != r.launch) return fail(HERMITE_EHIP, "run of many steps: no status");
         ++c->runs_on_chip;
-        if (!h.done) ++c->runs_given_up;
-        else if (h.handoff) ++c->runs_handed_off;
-        if (!h.done) return HERMITE_OK;
-        *launched += h.handoff ? h.steps : r.steps;
+        if (!h.done) {
+            ++c->runs_given_up;
+            return HERMITE_OK;
+        }
+        *launched += r.steps;
         *steps += h.steps;
         *interactions += h.interactions;
         if (h.bad)
             return fail(HERMITE_ENONFINITE,
                         "non-finite state after block time %lld ticks (e.g. coincident "
                         "particles with zero softening)", (long long)h.T);
-        if (h.handoff) return HERMITE_OK;
         if (h.na == 0 || h.T >= r.T_end) *done = 1;
         if (*done || (max_steps > 0 && *launched >= max_steps)) {
             *ended = true;

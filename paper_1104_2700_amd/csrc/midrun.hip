@@ -26,9 +26,8 @@
 // at the last step's when the next one's arrive), the others need one.
 //
 // No wait is without end, and a launch that is given up leaves the state as
-// it was: see smallrun.hip.  A block whose plan has chunks that do not tile
-// a slice ends the launch before it (handoff); none does with the default
-// tuning.
+// it was: see smallrun.hip.  So does a block whose plan has chunks that do not
+// tile a slice or have no room (none has with the default tuning's rules).
 //
 // The sums are the ones of the step-by-step path bit for bit: the plan's
 // lanes and chunks, its reduction's order, and the same corrector.
@@ -190,7 +189,7 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
     if (tid == 0) s_stop = r.patience < 0 ? 1 : 0;
     __syncthreads();
     int64_t T = 0, inter = 0, done_steps = 0, last_T = 0;
-    int32_t na = 0, last_na = 0, clamped = 0, bad = 0, handoff = 0;
+    int32_t na = 0, last_na = 0, clamped = 0, bad = 0;
     bool gave_up = s_stop != 0;
     int32_t to_check = r.check_every;
     // z / P, z < 65536
@@ -364,8 +363,8 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
             gave_up = true;
             break;
         }
-        if (plan == kNoPlan) {
-            handoff = 1;
+        if (plan == kNoPlan) {   // in every workgroup
+            gave_up = true;
             break;
         }
         const int lg = plan & 7, L = 1 << lg;
@@ -742,7 +741,6 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
         h->T = T;
         h->na = na;
         h->bad = bad;
-        h->handoff = handoff;
         h->launch = r.launch;
     }
 }

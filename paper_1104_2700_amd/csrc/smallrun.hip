@@ -369,7 +369,6 @@ __global__ void __launch_bounds__(64 * MAXW, 1) small_run_kernel(SmallRunArgs r)
         h->T = T;
         h->na = na;
         h->bad = bad;
-        h->handoff = 0;
         h->launch = r.launch;
     }
 }
