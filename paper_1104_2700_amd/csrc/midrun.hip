@@ -41,7 +41,12 @@ namespace hm {
 namespace {
 
 constexpr int kWaves = kMidThreads / 64;
-constexpr int kStage = 64;       // active particles of a row staged at a time
+// Active particles of a row staged at a time: 64 where their sums over a
+// slice's chunks wait in LDS, a particle a thread where they go straight out.
+// (There plans have few lanes and long chunks, and a wave takes 64 / lanes
+// particles and a chunk: from 64 particles one wave of the eight had work.
+// N = 16384: 8192 active 534 us a step, now 209; 4096 146, now 112.)
+constexpr int kStage = 64, kStageMax = kMidThreads;
 constexpr int kBatch = 64;       // active particles of a slice corrected at a time
 // From so many lines read by all copies on, the copies share the work: a
 // third exchange costs 1.5 to 3 us, and 65536 lines are 8 MB through the
@@ -138,8 +143,8 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
     constexpr int KP = kMidSlice / kMidThreads;    // particles of a thread
     constexpr int S = kMidSlice;
     __shared__ double s_p[7][S];                   // x, v at the block time; m
-    __shared__ double s_i[6][kStage];
-    __shared__ int32_t s_ii[kStage];
+    __shared__ double s_i[6][kStageMax];
+    __shared__ int32_t s_ii[kStageMax];
     __shared__ double s_c[kStage * (S / kTJ)][7];   // their sums over each chunk
     __shared__ double s_old[kBatch][7];            // dt, a, j
     __shared__ int32_t s_oi[kBatch];
@@ -194,6 +199,10 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
     int32_t to_check = r.check_every;
     // z / P, z < 65536
     auto by_rows = [&](int z) { return (int)__umulhi((uint32_t)z, e.rows_inverse); };
+    auto chunks = [&](int plan) {
+        const int lg = 8 + ((plan >> 3) & 3);   // log2 of a chunk (any value for kNoPlan)
+        return (n + (1 << lg) - 1) >> lg;
+    };
 
     for (int64_t step = 1; step <= r.steps && !gave_up; ++step) {
         const uint32_t tag = (uint32_t)(r.epoch + step);
@@ -313,9 +322,12 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
         // ---- the plan, the row's particles, the prediction ----------------------
         const int plan = e.plans[na];
         const int mine = na > p ? by_rows(na - 1 - p) + 1 : 0;   // positions p, p + P, ...
+        const int ch = chunks(plan);                        // of the system
+        const bool by_thread = thread_reduce(ch, na);
+        const int batch = by_thread ? kStageMax : kStage;
         auto stage = [&](int r0) {
             const int rr = r0 + tid, pos = p + P * rr;
-            if (64 * wave >= kStage || r0 + 64 * wave >= mine) return;
+            if (64 * wave >= batch || r0 + 64 * wave >= mine) return;
             int sl = 0, f = 0;
             for (int k = 0; k < Q; ++k) {
                 const int fk = __builtin_amdgcn_readlane(first, k);
@@ -369,7 +381,6 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
         }
         const int lg = plan & 7, L = 1 << lg;
         const int jc = kTJ << (plan >> 3);
-        const int ch = (n + jc - 1) >> (8 + (plan >> 3));   // chunks of the system
         constexpr int lS = 2;
         static_assert(kTJ == 256 && S == kTJ << lS, "a slice in tiles");
         const int lper = lS - (plan >> 3), per = 1 << lper;   // chunks of a slice
@@ -377,17 +388,16 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
         // ---- the sweep: a wave 64 / L of the row's particles and a chunk -------
         // (where the reduction is a butterfly over the chunks, a slice's chunks
         // are its first steps, taken here: a slice's sums then are one line)
-        const bool by_thread = thread_reduce(ch, na);
         const int sub = lane & (L - 1);
         const int G = 64 >> lg;
-        for (int r0 = 0; r0 < mine; r0 += kStage) {
+        for (int r0 = 0; r0 < mine; r0 += batch) {
             if (r0 > 0) {
                 __syncthreads();
                 stage(r0);
                 __syncthreads();
                 if (s_stop) break;
             }
-            const int cnt = min(kStage, mine - r0);
+            const int cnt = min(batch, mine - r0);
             const int items = ((cnt + G - 1) >> (6 - lg)) << lper;
             for (int it = wave; it < items; it += kWaves) {
                 const int grp = it >> lper, cc = it & (per - 1);
@@ -413,7 +423,7 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
                     }
                     A.add(B);
                 }
-                double* c = s_c[rr * per + cc];
+                double* c = s_c[by_thread ? 0 : rr * per + cc];
                 uint64_t* w = e.partial +
                     ((int64_t)g * e.partial_lines + ((r0 + rr) << lper) + cc) * kMidLine;
                 if (L >= 8) {

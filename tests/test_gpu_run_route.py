@@ -162,3 +162,20 @@ def test_runs_from_several_threads_use_the_chip(H):
     if errors:
         raise errors[0]
     assert counts == [(4, 0, 0)] * 4
+
+
+@pytest.mark.parametrize("n,na", [(2048, 2048), (9000, 4500), (12000, 10753), (16384, 1025),
+                                  (16384, 8193), (16384, 16384)])
+def test_large_blocks_in_one_launch(H, ctx, n, na):
+    """Blocks whose particles a row stages 64 or 512 at a time, with a
+    remainder, against single steps."""
+    s0, eps2, _ = _start(H, ctx, n)
+    params = H.dt_params(1e-9, H.DT_PAPER, 6, 12)   # who is due stays at 2^-12
+    g = torch.Generator().manual_seed(na)
+    s0.dt.fill_(1 << 14)
+    s0.dt[torch.randperm(n, generator=g)[:na].cuda()] = 1 << 8
+    before = _launches(H, ctx)
+    a = _run(H, ctx, s0, eps2, params, steps=12)
+    assert _launches(H, ctx) == (before[0] + 1, 0, 0)
+    assert ctx.counters()["n_act"] == na
+    _same(a, _run(H, ctx, s0, eps2, params, graph=False, steps=12))
