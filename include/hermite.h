@@ -290,7 +290,9 @@ int hermite_step(hermite_ctx* ctx, const hermite_state* s,
  * launches that dominates small systems; one system of n <= 16384 swept in
  * FP64 (with the default tuning) takes many steps in one launch instead,
  * whose workgroups wait for each other on the device (bounded: a launch that
- * cannot get the device's compute units is taken step by step).
+ * cannot get the device's compute units is taken step by step; so are, for
+ * sync_every steps at a time, runs of up to 1536 particles of which nearly all
+ * are due in every step).
  *
  * Block selection in a run (Section 2's block scheme): at the start of the
  * call the particles are ordered by step size (one pass over t and dt,

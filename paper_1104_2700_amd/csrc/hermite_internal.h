@@ -317,6 +317,15 @@ hipError_t launch_correct_reduce(const CorrectArgs& c, const SweepArgs& sa, hipS
 constexpr int kSmallRunMax = 1536;       // particles
 constexpr int kSmallRunGrid = 64;        // workgroups
 
+// Blocks of more interactions than this are faster as single steps, which use
+// the whole chip (and whose corrected particles do not all travel to all
+// workgroups); after so many of them in a row the launch ends, and the host
+// takes sync_every single steps before it tries again.  A step in the launch /
+// a single one: N = 1536, 768 active 20.8 / 19.5 us, 1536 active 36.2 / 25.4;
+// 1280, 640 active 18.0 / 16.9, all 31.3 / 22.9; 1024, 768 active 16.1 / 15.7.
+constexpr int64_t kSmallRunHeavy = 1000000;
+constexpr int kSmallRunHeavyRow = 8;
+
 // How long the workgroups of a launch of many steps wait for each other, in
 // ticks of the 100 MHz wall clock.  On a free chip all of them start within
 // tens of microseconds; where others hold compute units, the run goes on in
@@ -336,6 +345,7 @@ struct SmallRunStatus {
     int64_t T;           // the last block time selected (> T_end: the end)
     int64_t na;          // its active particles (0 past T_end)
     int64_t bad;         // a non-finite value was found
+    int64_t left;        // ended before r.steps: single steps are faster
 };
 
 struct SmallRunArgs {

@@ -1403,7 +1403,7 @@ static std::atomic<int> g_small_runs[64];
 // over or is to be taken step by step.
 static int run_launches(hermite_ctx* c, SmallRunArgs& r, int64_t launch_steps, int64_t* epoch,
                         int64_t max_steps, hipStream_t st, int64_t* launched, int64_t* steps,
-                        int64_t* interactions, int32_t* done, bool* ended,
+                        int64_t* interactions, int32_t* done, bool* ended, bool* left,
                         const std::function<int(bool*)>& launch)
 {
     // steps of a launch: the host's checks fall on its ends
@@ -1424,7 +1424,7 @@ static int run_launches(hermite_ctx* c, SmallRunArgs& r, int64_t launch_steps, i
             ++c->runs_given_up;
             return HERMITE_OK;
         }
-        *launched += r.steps;
+        *launched += h.left ? h.steps : r.steps;
         *steps += h.steps;
         *interactions += h.interactions;
         if (h.bad)
@@ -1432,6 +1432,8 @@ static int run_launches(hermite_ctx* c, SmallRunArgs& r, int64_t launch_steps, i
                         "non-finite state after block time %lld ticks (e.g. coincident "
                         "particles with zero softening)", (long long)h.T);
         if (h.na == 0 || h.T >= r.T_end) *done = 1;
+        *left = !*done && h.left;
+        if (*left) return HERMITE_OK;
         if (*done || (max_steps > 0 && *launched >= max_steps)) {
             *ended = true;
             return HERMITE_OK;
@@ -1441,15 +1443,16 @@ static int run_launches(hermite_ctx* c, SmallRunArgs& r, int64_t launch_steps, i
 
 // The run of one system in FP64 by launches of many steps each
 // (launch_small_run, launch_mid_run).  *launched counts the steps asked for;
-// *ended is set when the run is over (T_end, max_steps) and cleared when the
-// rest is to be taken step by step (not such a system, or a launch was given
-// up).
+// *ended is set when the run is over (T_end, max_steps) and cleared when it is
+// to go on step by step: for a while (*left: its blocks are ones that single
+// steps are faster for) or for the rest (not such a system, or a launch was
+// given up).
 static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int precision,
                      const hermite_dt_params* p, int64_t T_end, int32_t sync_every,
                      int64_t max_steps, hipStream_t st, int64_t* launched, int64_t* steps,
-                     int64_t* interactions, int32_t* done, bool* ended)
+                     int64_t* interactions, int32_t* done, bool* ended, bool* left)
 {
-    *ended = false;
+    *ended = *left = false;
     const int64_t n = s->n;
     const bool fp64 = precision == HERMITE_FP64 ||
                       ((precision == HERMITE_MIXED || precision == HERMITE_MIXED_2F) &&
@@ -1511,7 +1514,7 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
         r.xbuf = (double*)c->small_x.p;
         r.flags = (int64_t*)c->small_flags.p;
         return run_launches(c, r, 65536, &c->small_epoch, max_steps, st, launched, steps,
-                            interactions, done, ended, [&](bool* in) -> int {
+                            interactions, done, ended, left, [&](bool* in) -> int {
             std::shared_lock<std::shared_mutex> chip(g_chip[c->device], std::try_to_lock);
             struct Place {
                 std::atomic<int>& n;
@@ -1558,7 +1561,7 @@ static int small_run(hermite_ctx* c, const hermite_state* s, double eps2, int pr
     e.corrected = (uint64_t*)(base + head + row + all + part);
     e.verdict = (int64_t*)c->mid_flag.p;
     return run_launches(c, r, 4096, &c->mid_epoch, max_steps, st, launched, steps, interactions,
-                        done, ended, [&](bool* in) -> int {
+                        done, ended, left, [&](bool* in) -> int {
         std::unique_lock<std::shared_mutex> chip(g_chip[c->device], std::try_to_lock);
         if (!(*in = chip.owns_lock())) return HERMITE_OK;
         if ((r.epoch >> 32) != ((r.epoch + r.steps + 2) >> 32)) {
@@ -1587,31 +1590,37 @@ int hermite_run(hermite_ctx* c, const hermite_state* s, const hermite_clusters* 
         return fail(HERMITE_EINVAL, "T_end must be a non-negative multiple of 2^(tick_bits-k_min)");
     hipStream_t st = (hipStream_t)stream;
     int64_t launched = 0, small_steps = 0, small_inter = 0;
+    int64_t steps = 0, inter = 0;   // of the launches of many steps before c0
     int32_t done = 0;
-    if (!cl && use_graph && s->n <= kMidRunMax) {
+    bool chip = !cl && use_graph && s->n <= kMidRunMax, single = false;
+    if (chip) {
         CHECK(check_precision(precision));
         CHECK(check_eps2(eps2));
-        bool ended = false;
-        CHECK(small_run(c, s, eps2, precision, p, T_end, sync_every, max_steps, st, &launched,
-                        &small_steps, &small_inter, &done, &ended));
-        if (ended) {
-            if (steps_out) *steps_out = small_steps;
-            if (interactions_out) *interactions_out = small_inter;
-            if (done_out) *done_out = done;
-            return HERMITE_OK;
-        }
     }
-    int64_t c0[6], c1[6];
-    CHECK(hermite_counters(c, c0, stream));
-    // Select from the step-size order unless the sweep selects itself (one
-    // small system) or the clusters do not fit the selection's LDS tables.
     bool level = false;
-    if (!(cl == nullptr && s->n <= kFusedSelMax) && (!cl || cl->n_clusters <= kLdsClusters)) {
-        CHECK(check_clusters(cl, s->n));
-        CHECK(ensure_step_scratch(c, s->n));
-        CHECK(level_init(c, s, cl, p, st, &level));
-    }
+    int64_t c0[6], c1[6];
     for (;;) {
+        if (chip) {
+            bool ended = false;
+            CHECK(small_run(c, s, eps2, precision, p, T_end, sync_every, max_steps, st, &launched,
+                            &small_steps, &small_inter, &done, &ended, &chip));
+            if (ended) break;
+        }
+        if (!single) {
+            single = true;
+            steps = small_steps;
+            inter = small_inter;
+            CHECK(hermite_counters(c, c0, stream));
+            // Select from the step-size order unless the sweep selects itself
+            // (one small system) or the clusters do not fit the selection's
+            // LDS tables.
+            if (!(cl == nullptr && s->n <= kFusedSelMax) &&
+                (!cl || cl->n_clusters <= kLdsClusters)) {
+                CHECK(check_clusters(cl, s->n));
+                CHECK(ensure_step_scratch(c, s->n));
+                CHECK(level_init(c, s, cl, p, st, &level));
+            }
+        }
         int batch = sync_every;
         if (max_steps > 0 && launched + batch > max_steps) batch = (int)(max_steps - launched);
         int k = 0;
@@ -1645,9 +1654,16 @@ int hermite_run(hermite_ctx* c, const hermite_state* s, const hermite_clusters* 
         }
         if (max_steps > 0 && launched >= max_steps) break;
     }
-    CHECK(hermite_counters(c, c1, stream));
-    if (steps_out) *steps_out = small_steps + c1[0] - c0[0];
-    if (interactions_out) *interactions_out = small_inter + c1[1] - c0[1];
+    if (single) {
+        CHECK(hermite_counters(c, c1, stream));
+        steps += c1[0] - c0[0];
+        inter += c1[1] - c0[1];
+    } else {
+        steps = small_steps;
+        inter = small_inter;
+    }
+    if (steps_out) *steps_out = steps;
+    if (interactions_out) *interactions_out = inter;
     if (done_out) *done_out = done;
     return HERMITE_OK;
 }

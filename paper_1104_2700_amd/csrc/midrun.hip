@@ -751,6 +751,7 @@ __global__ void __launch_bounds__(kMidThreads) mid_run_kernel(SmallRunArgs r, Mi
         h->T = T;
         h->na = na;
         h->bad = bad;
+        h->left = 0;
         h->launch = r.launch;
     }
 }

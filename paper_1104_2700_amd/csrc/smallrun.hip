@@ -134,7 +134,7 @@ __global__ void __launch_bounds__(64 * MAXW, 1) small_run_kernel(SmallRunArgs r)
         (&s_part[0][0][0])[q] = 0.0;
     __syncthreads();
     int64_t T = 0, inter = 0, done_steps = 0, last_T = 0;
-    int32_t na = 0, last_na = 0, clamped = 0, bad = 0;
+    int32_t na = 0, last_na = 0, clamped = 0, bad = 0, heavy = 0, left = 0;
     bool gave_up = false;
 
     for (int64_t step = 1; step <= r.steps; ++step) {
@@ -308,6 +308,11 @@ __global__ void __launch_bounds__(64 * MAXW, 1) small_run_kernel(SmallRunArgs r)
             bad = __syncthreads_or(non_finite(x, v, a, jk) ? 1 : 0);
             if (bad) break;
         }
+        heavy = (int64_t)na * n > kSmallRunHeavy ? heavy + 1 : 0;
+        if (heavy == kSmallRunHeavyRow && step < r.steps) {
+            left = 1;
+            break;
+        }
     }
     if (!gave_up && !bad) bad = __syncthreads_or(non_finite(x, v, a, jk) ? 1 : 0);
 
@@ -369,6 +374,7 @@ __global__ void __launch_bounds__(64 * MAXW, 1) small_run_kernel(SmallRunArgs r)
         h->T = T;
         h->na = na;
         h->bad = bad;
+        h->left = left;
         h->launch = r.launch;
     }
 }

@@ -179,3 +179,43 @@ def test_large_blocks_in_one_launch(H, ctx, n, na):
     assert _launches(H, ctx) == (before[0] + 1, 0, 0)
     assert ctx.counters()["n_act"] == na
     _same(a, _run(H, ctx, s0, eps2, params, graph=False, steps=12))
+
+
+@pytest.mark.parametrize("n,na,launches", [(1536, 1536, 3), (1536, 652, 3), (1536, 651, 1),
+                                           (1024, 1024, 3), (900, 900, 1)])
+def test_small_systems_large_blocks_leave_the_chip(H, ctx, n, na, launches):
+    """More than 1e6 interactions a block: a launch ends after eight of them,
+    sync_every single steps follow, and another launch tries again; the state,
+    the counts and the end are the single steps'."""
+    s0, eps2, _ = _start(H, ctx, n)
+    params = H.dt_params(1e-9, H.DT_PAPER, 6, 12)
+    g = torch.Generator().manual_seed(na)
+    s0.dt.fill_(1 << 14)
+    s0.dt[torch.randperm(n, generator=g)[:na].cuda()] = 1 << 8
+    out = []
+    for graph in (True, False):
+        s = s0.clone()
+        c0 = ctx.counters()
+        res = ctx.run(s, eps2, params, 1 << TB, H.FP64, use_graph=graph, sync_every=16,
+                      max_steps=8 + 16 + 8 + 16 + 5, with_done=True)
+        c1 = ctx.counters()
+        out.append((s, res, [c1[k] - c0[k] for k in ("steps", "interactions", "clamped")], c1["T"]))
+        if graph:
+            assert _launches(H, ctx) == (launches, 0, 0)
+    _same(out[0][0], out[1][0])
+    assert out[0][1:] == out[1][1:] and out[0][1][0] == 53
+
+
+def test_a_run_that_leaves_the_chip_reaches_its_end(H, ctx):
+    n = 1536
+    s0, eps2, _ = _start(H, ctx, n)
+    params = H.dt_params(1e-9, H.DT_PAPER, 6, 12)
+    s0.dt.fill_(1 << 8)
+    for T_end in (1 << 14, 5 << 14):
+        out = []
+        for graph in (True, False):
+            s = s0.clone()
+            out.append((ctx.run(s, eps2, params, T_end, H.FP64, use_graph=graph, sync_every=5,
+                                with_done=True), s))
+        assert out[0][0] == out[1][0] and out[0][0][0] == T_end >> 8 and out[0][0][2]
+        _same(out[0][1], out[1][1])
