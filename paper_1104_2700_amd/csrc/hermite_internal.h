@@ -33,6 +33,7 @@ struct SweepPlan {
     int32_t total_items;  // work items (cluster, i-tile, j-chunk)
     int32_t fp64_all;     // mixed precisions: this block is swept in FP64 (its
                           // interactions are below SweepArgs::fp64_inter_below)
+    int32_t queue;        // items that workgroups have taken beyond their first
 };
 
 // Everything the plan, sweep and reduce kernels read.  Passed by value.
@@ -71,12 +72,14 @@ struct SweepArgs {
     // kernel runs, and the reduce stage counts the interactions).
     int32_t host_plan;
     SweepPlan hp;
-    // The tuning is the default one: one system's split is chosen for its
+    int32_t item_grid;         // nonzero: a workgroup per work item of hp
+    int32_t short_chunks;      // the sweep's chunks may follow split_short
+    // The tuning is the default one: one system's FP64 split is chosen for its
     // sizes (split_for_sizes) from the kernel's cost per pair and its
     // resident workgroups per compute unit.
     int32_t auto_split;
     int32_t n_cu;
-    int32_t split_fp64;        // the sweep is FP64
+    int32_t split_fp64;        // the sweep is FP64, and these are its figures
     int32_t split_tiles;       // nonzero: chunks of a power of two of tiles, this
                                // many at most (where the partial sums have room)
     int32_t split_res;
@@ -166,8 +169,8 @@ hipError_t launch_force(const SweepArgs& a, const SweepArgs* ra, int precision, 
                         int grid, bool pot_only, hipStream_t st,
                         const hipEvent_t* marks = nullptr);
 
-// Sets the split model's kernel figures (split_*) of a sweep.
-void set_split_model(SweepArgs* a, int precision, int variant, bool pot_only);
+// Sets the split model's kernel figures (split_*) of an FP64 sweep.
+void set_split_model(SweepArgs* a, int variant, bool pot_only);
 
 // The plan launch_force makes on the host for a sweep of one system whose
 // active count the host knows (a->n_clusters == 1, no n_act_dev; a->ipl set).

@@ -338,9 +338,10 @@ void fill_sweep(const SweepScratch& sc, int n_cu, const hermite_state* s, const 
     a->auto_split = std::memcmp(&tu, &def, sizeof def) == 0 ? 1 : 0;
     if (a->auto_split && a->n_clusters == 1) {   // (one cluster is planned as a system is)
         const bool mixed = precision == HERMITE_MIXED || precision == HERMITE_MIXED_2F;
-        const bool small = mixed && s->n < fp64_below;   // swept in FP64
-        set_split_model(a, small ? HERMITE_FP64 : precision, small ? tu.variant & 1 : tu.variant,
-                        false);
+        if (precision == HERMITE_FP64 || (mixed && s->n < fp64_below))   // swept in FP64
+            set_split_model(a, tu.variant & 1, false);
+        else
+            a->short_chunks = mixed ? 1 : 0;
     }
     a->near_factor = precision == HERMITE_FP64 ? 0.0 : near_factor;
     a->fp64_below = precision == HERMITE_FP64 ? 0 : fp64_below;
@@ -385,8 +386,9 @@ void fill_refine(const SweepScratch& sc, const SweepArgs& a, int variant, SweepA
     ra->partial = sc.partial;
     ra->partial_cap = sc.partial_cap;
     ra->refine = 0;
+    ra->short_chunks = 0;
     ra->defer_fp64 = 0;
-    if (ra->auto_split && ra->n_clusters == 1) set_split_model(ra, HERMITE_FP64, variant & 1, false);
+    if (ra->auto_split && ra->n_clusters == 1) set_split_model(ra, variant & 1, false);
     ra->near_factor = 0.0;
     ra->fp64_below = 0;
     ra->fp64_inter_below = 0;

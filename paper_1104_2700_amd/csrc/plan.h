@@ -419,7 +419,7 @@ __host__ __device__ __forceinline__ bool thread_reduce(int s_max, int na)
     return s_max <= kWaveReduceChunks || na >= kThreadReduceMinAct;
 }
 
-// A model of a sweep's time (microseconds) for na active particles of one
+// A model of an FP64 sweep's time (microseconds) for na active particles of one
 // system, L lanes a particle and about items_want work items; *jc gets the
 // chunk length.  A tile costs a wave (kTJ / L) ipl pair evaluations of
 // split_cyc cycles and about 800 more (two barriers, the staging); split_res
@@ -428,10 +428,9 @@ __host__ __device__ __forceinline__ bool thread_reduce(int s_max, int na)
 // uneven finish of the last round; then the partial sums' way through the
 // reduction.  It balances items that fill the last round of resident
 // workgroups against rounds so short that a thin last one costs little.
-// (N = 65536, chunks x lanes, plan_split's / this choice: 3001 active mixed
-// 26 x 8 250 us / 43 x 8 226; FP64 43 x 8 259 / 32 x 4 254; 333 active FP64
-// 128 x 8 both; 65536 active mixed 10 x 1 4.11 / 16 x 1 3.90 ms; N = 16384,
-// 3000 active FP64 85 / 73.)
+// (N = 65536, chunks x lanes, plan_split's / this choice: 3001 active 43 x 8
+// 259 us / 32 x 4 254; 333 active 128 x 8 both; N = 16384, 3000 active 85 / 73.
+// The mixed precisions' sweeps don't follow it: see split_short.)
 __host__ __device__ inline float split_cost(const SweepArgs& a, int32_t na, int32_t L,
                                             int64_t items_want, int64_t* jc)
 {
@@ -456,9 +455,7 @@ __host__ __device__ inline float split_cost(const SweepArgs& a, int32_t na, int3
     const int64_t R = (int64_t)a.n_cu * a.split_res;
     const int64_t items = tiles * ch, full = div_floor(items, R), rem = items - full * R;
     const int q = (int)div_ceil(rem, a.n_cu);
-    const float rest = q == 0 ? 0.0f
-                     : a.split_fp64 ? (q == 1 ? 0.27f : q == 2 ? 0.10f : 0.0f)
-                                    : (q == 1 ? 0.84f : q == 2 ? 0.40f : q == 3 ? 0.24f : 0.0f);
+    const float rest = q == 1 ? 0.27f : q == 2 ? 0.10f : 0.0f;
     const float part = ((float)q + rest) / (float)a.split_res;
     const float rounds = (float)full + (part < 1.0f ? part : 1.0f);
     const float wave = (float)(kTJ / L * a.ipl) * a.split_cyc + 800.0f;
@@ -478,22 +475,18 @@ __host__ __device__ inline int64_t split_items(const SweepArgs& a, int k)
                                     : (k - 3) * a.split_res);
 }
 
-// FP64 sweeps may take any number of lanes whose tiles are not mostly
-// empty; the mixed modes keep plan_split's (*L), which their FP32 runs follow.
-__host__ __device__ inline bool split_lanes_ok(const SweepArgs& a, int32_t na, int32_t L,
-                                               int32_t L_plan)
+// Any number of lanes whose tiles are not mostly empty.
+__host__ __device__ inline bool split_lanes_ok(const SweepArgs& a, int32_t na, int32_t L)
 {
-    if (!a.split_fp64) return L == L_plan;
     return L == 64 || (int64_t)a.ipl * (kWG / L) <= 2 * (int64_t)na;
 }
 
 // The split of least modelled time (host).
 inline void split_for_sizes(const SweepArgs& a, int32_t na, int32_t* L_io, int64_t* jc_io)
 {
-    const int32_t L_plan = *L_io;
     float best = 3.0e38f;
     for (int32_t L = 1; L <= 64; L <<= 1) {
-        if (!split_lanes_ok(a, na, L, L_plan)) continue;
+        if (!split_lanes_ok(a, na, L)) continue;
         for (int k = 0; k < kSplitCands; ++k) {
             int64_t jc;
             const float t = split_cost(a, na, L, split_items(a, k), &jc);
@@ -512,7 +505,7 @@ inline void split_for_sizes(const SweepArgs& a, int32_t na, int32_t* L_io, int64
 // 18.9; 1024 of 1024 12.6 / 11.9).
 constexpr int64_t kSplitMinInter = 1000000;
 
-// FP64 sweeps of 6e7 interactions or more keep it too: there the model takes
+// Sweeps of 6e7 interactions or more keep it too: there the model takes
 // plan_split's last round for longer than it is (N = 28422, 7105 active: 784
 // items on 768 places 263 us, the model's choice 268; N = 22000, 7333: 208 /
 // 213; N = 40000, 6666: 350 / 357; N = 53850, 26842: 1.73 / 1.80 ms; though
@@ -523,8 +516,36 @@ constexpr int64_t kSplitKeepFrom = 60000000;
 __host__ __device__ __forceinline__ bool split_by_model(const SweepArgs& a, int32_t na)
 {
     const int64_t inter = (int64_t)na * a.n;
-    if (!a.auto_split || inter < kSplitMinInter) return false;
-    return !a.split_fp64 || a.split_tiles > 0 || inter < kSplitKeepFrom;
+    if (!a.auto_split || !a.split_fp64 || inter < kSplitMinInter) return false;
+    return a.split_tiles > 0 || inter < kSplitKeepFrom;
+}
+
+// Mixed sweeps of one system in FP32 pair arithmetic from this many
+// interactions on (the default policy sweeps fewer than 5e7 in FP64; not
+// measured below): chunks as short as the partial sums have room for, down to
+// a tile.  Their workgroups take items as they get free (a workgroup an item
+// where the host knows their number, else from a counter), and fill the chip
+// more evenly the more there are; of a fixed grid's 1280 workgroups only 1024
+// (MIXED_2F: 768) have a place, and those that start late are late by a whole
+// share.  plan_split's about 1280 items / this, us: MIXED, 1500 of 33000
+// 95 / 75, 9000 405 / 382, all 1217 / 1097, 4500 of 45000 311 / 256, 3001 of
+// 65536 254 / 234, 22500 1529 / 1353, all 4063 / 3696, 2200 of 131072
+// 372 / 339; MIXED_2F, 9000 of 33000 457 / 438, all 1376 / 1269, 2200 of 65536
+// 241 / 213, all 4392 / 4106.
+constexpr int64_t kShortChunksFrom = 30000000;
+
+__host__ __device__ __forceinline__ bool split_short(const SweepArgs& a, int32_t na)
+{
+    const int64_t inter = (int64_t)na * a.n;
+    return a.short_chunks && inter >= kShortChunksFrom && inter >= a.fp64_inter_below;
+}
+
+__host__ __device__ inline int64_t shortest_chunk(const SweepArgs& a, int32_t na)
+{
+    const int64_t tiles = (a.n + kTJ - 1) / kTJ;
+    int64_t room = div_floor(a.partial_cap, kRows * (int64_t)na);
+    if (room < 1) room = 1;
+    return div_ceil(tiles, room < tiles ? room : tiles) * kTJ;
 }
 
 // The same by a wave (every lane calls it): lane 8 l + k takes 2^l lanes and
@@ -536,7 +557,7 @@ __device__ inline void split_for_sizes_wave(const SweepArgs& a, int32_t na, int3
     const int32_t L = 1 << (lane / kSplitCands < 6 ? lane / kSplitCands : 6);
     int64_t jc;
     float t = split_cost(a, na, L, split_items(a, lane % kSplitCands), &jc);
-    if (lane >= 7 * kSplitCands || !split_lanes_ok(a, na, L, *L_io)) t = 3.0e38f;
+    if (lane >= 7 * kSplitCands || !split_lanes_ok(a, na, L)) t = 3.0e38f;
     const float m = wave_min(t);
     const int w = __builtin_ctzll(__ballot(t == m) | (1ull << 63));
     const int lo = __builtin_amdgcn_readlane((int)jc, w);
@@ -618,6 +639,7 @@ __device__ inline void plan_body(const SweepArgs& a, int32_t na_in,
         plan_split_wave(a, na, 1, &L, &ti, &jc);
         if (split_by_model(a, na))
             split_for_sizes_wave(a, na, &L, &ti, &jc);
+        if (split_short(a, na)) jc = shortest_chunk(a, na);
         if (tid == 0) {
             const int32_t tiles = (int32_t)div_ceil_p2(na, ti);
             const int32_t ch = na > 0 ? (int32_t)div_ceil(a.n, jc) : 0;
@@ -633,6 +655,7 @@ __device__ inline void plan_body(const SweepArgs& a, int32_t na_in,
             P->s_max = ch;
             P->jc = jc;
             P->total_items = tiles * ch;
+            P->queue = 0;
             P->fp64_all = (a.fp64_inter_below > 0 && (int64_t)na * a.n < a.fp64_inter_below) ? 1 : 0;
             if (a.counters && na > 0)
                 atomicAdd((unsigned long long*)&a.counters[1],

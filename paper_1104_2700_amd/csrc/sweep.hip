@@ -830,7 +830,13 @@ sweep_kernel(SweepArgs a)
     const int C = a.n_clusters;
     const int64_t n = a.n;
 
-    // Workgroup w takes items w, w + grid, w + 2 grid, ...
+    // Workgroup w takes items w, w + grid, w + 2 grid, ..., or (the mixed
+    // precisions' device plans of one system) w and then the next one that
+    // nobody has.  (Asked for at an item's end: while it is swept, the one
+    // asked for would wait for it.)
+    constexpr bool kQueue = kMixed && PREC != 3 && !SEL && !HOST;
+    __shared__ int32_t s_next;
+    const bool queue = kQueue && a.short_chunks && total > (int)gridDim.x;
     int item = blockIdx.x;
     for (;; ) {
         if (item >= total) break;
@@ -1052,8 +1058,17 @@ sweep_kernel(SweepArgs a)
                 }
             }
         }
-        // further items round-robin: a shared counter would serialise every
-        // fetch on one address (tens of ns each across the chip)
+        if constexpr (kQueue) {
+            if (queue) {
+                if (tid == 0) s_next = (int)gridDim.x + atomicAdd(&P->queue, 1);
+                __syncthreads();
+                item = s_next;
+                continue;
+            }
+        }
+        // round-robin: a shared counter would serialise every fetch on one
+        // address (tens of ns each across the chip), which FP64's longer
+        // chunks and the ensembles' small items do not repay
         item += (int)gridDim.x;
         __syncthreads();   // the next item restages the LDS tile
     }
@@ -1262,15 +1277,13 @@ int sweep_occupancy(int precision, int variant, bool pot_only)
     return nb;
 }
 
-void set_split_model(SweepArgs* a, int precision, int variant, bool pot_only)
+void set_split_model(SweepArgs* a, int variant, bool pot_only)
 {
-    // cycles of a SIMD per wave and pair: FP64 33 instructions of four
-    // cycles and v_rsq_f64 of 16; the mixed modes' FP64 differences and
-    // conversions of four, FP32 of two
-    static const float cyc[4] = {148.0f, 112.0f, 125.0f, 95.0f};
-    a->split_fp64 = precision == 0 ? 1 : 0;
-    a->split_cyc = pot_only ? 68.0f : cyc[precision];
-    a->split_res = sweep_occupancy(precision, variant, pot_only);
+    // cycles of a SIMD per wave and pair: 33 FP64 instructions of four cycles
+    // and v_rsq_f64 of 16
+    a->split_fp64 = 1;
+    a->split_cyc = pot_only ? 68.0f : 148.0f;
+    a->split_res = sweep_occupancy(0, variant, pot_only);
 }
 
 int max_plan_items(const SweepArgs& a)
@@ -1303,7 +1316,11 @@ void launch_sweep_kernels(SweepArgs a, int precision, int variant, int grid, boo
         a.kind = kind;
         SweepFn f = sel ? sweep_sel_fn(prec, variant)
                         : sweep_fn(prec, variant, pot_only, a.host_plan != 0);
-        hipLaunchKernelGGL(f, dim3(grid), dim3(kWG), 0, st, a);
+        // workgroups that take items from the counter: as many as have a place
+        // (one that waits for another's end would hold its first item till then)
+        const bool queue = !sel && !a.host_plan && a.short_chunks && prec != 0;
+        const int places = queue ? a.n_cu * sweep_occupancy(prec, variant, false) : grid;
+        hipLaunchKernelGGL(f, dim3(places < grid ? places : grid), dim3(kWG), 0, st, a);
     };
     const bool mixed = !pot_only && (precision == 1 || precision == 2);
     const bool straddle = a.n_clusters > 1 && a.fp64_below > 1;
@@ -1367,11 +1384,14 @@ bool make_host_plan(SweepArgs* a, int precision, int variant, bool pot_only)
     int32_t L, ti;
     int64_t jc;
     plan_split(*a, na, 1, &L, &ti, &jc);
-    if (a->auto_split && fp64) set_split_model(a, 0, variant & 1, pot_only);
+    a->split_fp64 = 0;
+    if (a->auto_split && fp64) set_split_model(a, variant & 1, pot_only);
     if (split_by_model(*a, na)) {
         split_for_sizes(*a, na, &L, &jc);
         ti = a->ipl * (kWG / L);
     }
+    a->item_grid = !fp64 && split_short(*a, na) ? 1 : 0;
+    if (a->item_grid) jc = shortest_chunk(*a, na);
     a->host_plan = 1;
     a->hp.n_act = na;
     a->hp.L = L;
@@ -1480,7 +1500,7 @@ hipError_t launch_force(const SweepArgs& a_in, const SweepArgs* ra, int precisio
             refine = false;
             a.refine = 0;
         }
-        if (a.hp.total_items < grid) grid = a.hp.total_items;
+        if (a.item_grid || a.hp.total_items < grid) grid = a.hp.total_items;
     }
     // with refinement, a block the plan puts in FP64 is swept by the refine
     // sweep's launch (the whole block as its list) and scattered from there
