@@ -406,7 +406,11 @@ int hermite_set_tuning(hermite_ctx* ctx, int precision,
  * context and, if cache_path is non-NULL, merges it into that JSON file
  * keyed by device architecture, HIP version, precision and power-of-two
  * size buckets of n and n_act, with its time and the HBM bytes its j-split
- * adds (partial sums written and read back).  Synchronises. */
+ * adds (partial sums written and read back).  Synchronises.  A context with
+ * another tuning than the default, from here or hermite_set_tuning, takes the
+ * shape it states: the default's choices by size, and hermite_run's many steps
+ * in one launch, are then not made, and runs of one small system are up to
+ * three times slower than with the default. */
 int hermite_autotune(hermite_ctx* ctx, const hermite_state* s,
                      const hermite_clusters* cl, double eps2, int precision,
                      int32_t n_act, const char* cache_path, void* stream);

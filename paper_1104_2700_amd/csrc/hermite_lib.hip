@@ -232,11 +232,14 @@ hermite_tuning default_tuning(const hermite_ctx* c, int precision)
 // HERMITE_MIXED_2F sum the pairs within this radius in FP64.  Systems
 // smaller than fp64_below are swept in FP64 altogether: up to about 2^15
 // particles the FP64 sweep of all of them takes no longer than the FP32 one
-// with its near field and refinement (MI355X, default launch shapes: FP64 /
-// mixed 0.019 / 0.042 ms at N = 1024, 0.044 / 0.074 at 4096, 0.364 / 0.354
-// at 16384; 5.07 / 4.04 at 65536), and whole runs take the mixed path's
+// with its near field and refinement (MI355X, default launch shapes, one-sided
+// FP64 / mixed 0.019 / 0.042 ms at N = 1024, 0.044 / 0.074 at 4096, 0.364 /
+// 0.354 at 16384; 4.95 / 3.66 at 65536), and whole runs take the mixed path's
 // extra launches on every block step (N = 16384, t = 0 -> 1: 6.7 s against
-// 5.2 s in FP64).  The paper-faithful
+// 5.2 s in FP64).  (The line is drawn for blocks and block steps.  A call on
+// every particle that goes by pairs is faster in FP64 above it too, 3.17 ms at
+// 65536: a caller who wants that asks for FP64; MIXED keeps its arithmetic.)
+// The paper-faithful
 // mode keeps the printed scheme: radius 0 (only the self pair and
 // coincident particles take the FP64 path) and no FP64 systems.
 double default_near_factor(int precision)

@@ -5,7 +5,7 @@
 // particles), and a step is then the latency of three kernels: 17 us at
 // N = 1600, 20.5 at 4096, 22.6 at 16384 against 0.1, 0.3 and 2 us of
 // arithmetic.  Here P rows of Q workgroups, one a compute unit, stay for a
-// whole batch of steps: 11.4, 12.6 and 14.7 us.  Workgroup (p, q) holds slice
+// whole batch of steps: 10.9, 10.9 and 14.7 us.  Workgroup (p, q) holds slice
 // q of the particles (registers; what the sweep reads, predicted, in LDS), so
 // every row holds the whole system; row p sweeps the active positions p,
 // p + P, ..., each of its workgroups over its slice, and every workgroup

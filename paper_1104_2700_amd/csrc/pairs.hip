@@ -6,10 +6,10 @@
 // v - b r), the v_rsq_f64 and 8 for each side: 20 and half a v_rsq_f64 per
 // interaction, 88 cycles of a SIMD against 148.  Both sweeps are bound by
 // FP64 issue at the clock that the chip holds under it (about 2.0 GHz), so
-// the count is the time.  Measured (MI355X, default shapes, one-sided / by
-// pairs): N = 65536 4.93 / 3.24 ms, N = 9973 148 / 128 us, 256 clusters of
-// 263 ... 8080 particles 4.5 / 2.3 ms; potentials alone (the energy sweep)
-// N = 50021 1.53 / 0.80 ms.
+// the count is the time.  Measured (MI355X, default shapes, whole calls,
+// one-sided / by pairs): N = 65536 4.95 / 3.17 ms, N = 9973 129 / 112 us, 256
+// clusters of 263 ... 8080 particles 4.68 / 2.18 ms; potentials alone (the
+// energy sweep) N = 50021 1.50 / 0.77 ms.
 //
 // Layout.  A workgroup of W waves holds an i-block of 64 K W particles in
 // registers (K per lane, with their seven sums) and streams j tiles of 64 W
@@ -22,7 +22,7 @@
 // K = 4 keeps the 7 LDS reads and 7 LDS adds of a step (28 and 56 cycles of
 // the unit's LDS) well under its 4 x 176 FP64 cycles; moving j and its sums
 // between lanes by DPP would add 28 moves of four cycles to a step.  Four
-// particles a lane take 229 registers: two waves a SIMD.  (Reading the next
+// particles a lane take up to 241 registers: two waves a SIMD.  (Reading the next
 // step's j or the next tile ahead, and LDS read-modify-write in place of the
 // adds, measured the same or 3 % slower.)
 //
@@ -85,7 +85,7 @@ constexpr int64_t kPairMin = 6000, kPairMinPot = 4500;
 constexpr int64_t kPairFour = 20000;
 constexpr int64_t kPairWide = 45000, kPairWidePot = 24576;
 constexpr int64_t kPairMaxN = (int64_t)1 << 23;   // rows of at most 2^15 - 1 tiles
-// Ensembles whose largest cluster fits 43 blocks (16 chunks and 21 block
+// Ensembles whose largest cluster fits 43 blocks (17 chunks and 21 block
 // slots of partial sums), with at least 6e7 interactions (n^2 / C, a lower
 // bound; 4e7 from 30 clusters on, which fill the last round more evenly) and
 // clusters of 256 particles on average (1500 of 30 ... 300: 105 one-sided,

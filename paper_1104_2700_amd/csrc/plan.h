@@ -810,8 +810,9 @@ __device__ __forceinline__ void count_host_plan(const SweepArgs& a)
                   (unsigned long long)((int64_t)a.hp.n_act * a.n));
 }
 
-// Where the partial sums are: row r of position p over chunk k.  A thread a particle reads rows of all positions; a wave a particle reads,
-// and a sweep's lanes store, lines of a position's eight rows (from rows it
+// Where the partial sums are: row r of position p over chunk k.  A thread a
+// particle reads rows of all positions; a wave a particle reads, and a sweep's
+// lanes store, lines of a position's eight rows (from rows it
 // took a sector of every row and chunk for eight bytes: 333 of 65536
 // particles, 128 chunks, 45.0 us by rows, 41.5 by lines; a thread a particle
 // the other way round: 1200 of 5000 19.1 / 21.9).
